@@ -46,7 +46,8 @@ ADJ_OPS = {"l2sq": 12, "gram": 8}
 
 
 # the sources the tile kernel, its launch arguments and its plan are built from
-TILE_SOURCES = ("common.hpp", "kernels.hip", "launch.hpp", "plan.cpp", "plan.hpp", "tile.hpp")
+TILE_SOURCES = ("common.hpp", "kernels.hip", "launch.hpp", "plan.cpp", "plan.hpp", "strips.hip",
+                "tile.hpp")
 
 
 def kernel_source_digest():

@@ -141,8 +141,12 @@ struct PlanTag {
                shape_flags == o.shape_flags;
     }
 };
+struct PlanRecord {
+    PlanTag tag;
+    StripLaunch strips;  // waves > 0: a strip plan
+};
 std::mutex g_plan_mu;
-std::unordered_map<const void *, PlanTag> g_plan_tags;
+std::unordered_map<const void *, PlanRecord> g_plan_tags;
 
 PlanTag plan_tag(int kind, const pcf_set *X, const pcf_window *w, int64_t ldo, uint32_t flags)
 {
@@ -163,20 +167,36 @@ PlanTag plan_tag(int kind, const pcf_set *X, const pcf_window *w, int64_t ldo, u
     return t;
 }
 
-void remember_plan(const void *ws, const PlanTag &tag)
+// A plan's strip launch (waves = 0 for a tile plan).
+StripLaunch strip_launch(const Plan &plan, int rec_bytes)
 {
-    std::lock_guard<std::mutex> lock(g_plan_mu);
-    g_plan_tags[ws] = tag;
+    StripLaunch l;
+    if (!plan.strips)
+        return l;
+    l.waves = plan.strip_waves;
+    l.lds_bytes = kStripSharedBytes +
+                  l.waves * strip_wave_bytes(plan.strip_pairs, plan.strip_cols) +
+                  (plan.strip_row_recs + plan.strip_ring_recs) * rec_bytes;
+    const int cus = device_cus();
+    l.grid = plan.ntiles < cus ? (int)plan.ntiles : cus;
+    return l;
 }
 
-pcf_status check_reused_plan(const void *ws, const PlanTag &tag)
+void remember_plan(const void *ws, const PlanTag &tag, const StripLaunch &strips)
+{
+    std::lock_guard<std::mutex> lock(g_plan_mu);
+    g_plan_tags[ws] = {tag, strips};
+}
+
+pcf_status check_reused_plan(const void *ws, const PlanTag &tag, StripLaunch &strips)
 {
     std::lock_guard<std::mutex> lock(g_plan_mu);
     auto it = g_plan_tags.find(ws);
     if (it == g_plan_tags.end())
         return fail(PCF_EINVAL, "PCF_REUSE_PLAN: this workspace holds no plan made by "
                                 "this library");
-    const PlanTag &h = it->second;
+    const PlanTag &h = it->second.tag;
+    strips = it->second.strips;
     if (h.kind != tag.kind) {
         static const char *names[] = {"a matrix call", "pcf_pairwise_backward",
                                       "pcf_pairwise_batched", "pcf_cross"};
@@ -214,7 +234,7 @@ pcf_status upload_plan(const Plan &plan, int rec_bytes, void *ws,
         e = hipStreamSynchronize(s);  // buf is a local
     if (e != hipSuccess)
         return hip_fail(e, "uploading the tile plan");
-    remember_plan(ws, tag);
+    remember_plan(ws, tag, strip_launch(plan, rec_bytes));
     return PCF_OK;
 }
 
@@ -246,6 +266,7 @@ struct Call {
     bool reuse;
     bool validate;
     int64_t P;  // rows, -1 when unknown (plan reused)
+    StripLaunch strips;  // the plan's (waves = 0: a tile plan)
 };
 
 pcf_status prepare(const pcf_set *X, const Plan *plan, void *ws,
@@ -260,8 +281,9 @@ pcf_status prepare(const pcf_set *X, const Plan *plan, void *ws,
                                     ws_bytes, s, tag);
         if (st != PCF_OK)
             return st;
+        c.strips = strip_launch(*plan, rec_bytes_of(X->dtype));
     } else {
-        pcf_status st = check_reused_plan(ws, tag);
+        pcf_status st = check_reused_plan(ws, tag, c.strips);
         if (st != PCF_OK)
             return st;
     }
@@ -338,11 +360,17 @@ pcf_status forward_common(const pcf_set *X, pcf_kind kind, double p, void *out,
         if (st != PCF_OK)
             return st;
         std::string err;
-        if (!plan_matrix(X->n, ho, rec_bytes_of(X->dtype), false, w != nullptr,
-                         w ? w->row0 : 0, w ? w->row1 : 0, w ? w->col0 : 0,
-                         w ? w->col1 : 0, (flags & PCF_UPPER_ONLY) != 0, ldo,
-                         shape_of(flags), plan, err))
-            return fail(PCF_EINVAL, err);
+        // (a workspace sized for the tile plan keeps it)
+        for (int cus = device_cus();; cus = 0) {
+            if (!plan_matrix(X->n, ho, rec_bytes_of(X->dtype), false, w != nullptr,
+                             w ? w->row0 : 0, w ? w->row1 : 0, w ? w->col0 : 0,
+                             w ? w->col1 : 0, (flags & PCF_UPPER_ONLY) != 0, ldo,
+                             shape_of(flags), plan, err, cus))
+                return fail(PCF_EINVAL, err);
+            if (cus == 0 ||
+                plan_workspace_bytes(plan, rec_bytes_of(X->dtype)) <= (int64_t)ws_bytes)
+                break;
+        }
     }
     Call c;
     st = prepare(X, reuse ? nullptr : &plan, ws, ws_bytes, flags, s, c, ho,
@@ -369,8 +397,10 @@ pcf_status forward_common(const pcf_set *X, pcf_kind kind, double p, void *out,
     }
     if (accumulate && a.root != 0)
         return fail(PCF_EINVAL, "a term of a sum takes no root");
-    hipError_t e = launch_forward(X->dtype == PCF_F64, hk, a,
-                                  tile_grid(reuse ? nullptr : &plan, reuse), s);
+    hipError_t e = c.strips.waves > 0
+                       ? launch_strips(X->dtype == PCF_F64, hk, a, c.strips, s)
+                       : launch_forward(X->dtype == PCF_F64, hk, a,
+                                        tile_grid(reuse ? nullptr : &plan, reuse), s);
     if (e != hipSuccess)
         return hip_fail(e, "tile kernel launch");
     return PCF_OK;
@@ -379,7 +409,7 @@ pcf_status forward_common(const pcf_set *X, pcf_kind kind, double p, void *out,
 // The combined CSR of X then Y (host), and the plan of the window
 // [0, nx) x [nx, nx + ny) over it.
 pcf_status cross_plan(const pcf_set *X, const pcf_set *Y, int64_t ldo, uint32_t flags,
-                      hipStream_t s, std::vector<int64_t> &comb, Plan &plan)
+                      hipStream_t s, std::vector<int64_t> &comb, Plan &plan, int cus)
 {
     std::vector<int64_t> xb, yb;
     const int64_t *xo = X->offsets_host, *yo = Y->offsets_host;
@@ -396,7 +426,7 @@ pcf_status cross_plan(const pcf_set *X, const pcf_set *Y, int64_t ldo, uint32_t 
         comb[nx + i] = xo[nx] + yo[i];
     std::string err;
     if (!plan_matrix(nx + ny, comb.data(), rec_bytes_of(X->dtype), false, true, 0, nx,
-                     nx, nx + ny, false, ldo, shape_of(flags), plan, err))
+                     nx, nx + ny, false, ldo, shape_of(flags), plan, err, cus))
         return fail(PCF_EINVAL, err);
     return PCF_OK;
 }
@@ -587,8 +617,9 @@ pcf_status noalloc_forward(const pcf_set *X, pcf_kind kind, double p, void *out,
 
 // Exact workspace of a forward call's plan (the size forward_common uploads
 // and packs), without touching a device when X->offsets_host is given.
+// (of its tile plan; with `bound`, enough for either kind of plan)
 pcf_status noalloc_plan_bytes(const pcf_set *X, const pcf_window *w, int64_t ldo,
-                              uint32_t flags, int64_t *bytes)
+                              uint32_t flags, int64_t *bytes, bool bound = false)
 {
     pcf_status st = check_set(X);
     if (st != PCF_OK)
@@ -608,7 +639,8 @@ pcf_status noalloc_plan_bytes(const pcf_set *X, const pcf_window *w, int64_t ldo
                      (flags & PCF_UPPER_ONLY) != 0, ldo > 0 ? ldo : 1, shape_of(flags), plan,
                      err))
         return fail(PCF_EINVAL, err);
-    *bytes = plan_workspace_bytes(plan, rec_bytes_of(X->dtype));
+    *bytes = bound ? plan_workspace_bound(plan, rec_bytes_of(X->dtype))
+                   : plan_workspace_bytes(plan, rec_bytes_of(X->dtype));
     return PCF_OK;
 }
 
@@ -623,7 +655,7 @@ pcf_status terms_layout(const pcf_set *X, const pcf_window *w, uint32_t flags,
 {
     int64_t fb = 0;
     const int64_t ldo = w ? (w->col1 - w->col0) : X->n;
-    pcf_status st = noalloc_plan_bytes(X, w, ldo, flags & ~(uint32_t)PCF_UPPER_ONLY, &fb);
+    pcf_status st = noalloc_plan_bytes(X, w, ldo, flags & ~(uint32_t)PCF_UPPER_ONLY, &fb, true);
     if (st != PCF_OK)
         return st;
     std::vector<int64_t> obuf;
@@ -856,11 +888,17 @@ pcf_status pcf_pairwise_batched(int32_t B, const int64_t *set_offsets_host,
         if (st != PCF_OK)
             return st;
         std::string err;
-        if (!plan_batched(B, set_offsets_host, out_offsets_host, ho, all->n,
-                          rec_bytes_of(all->dtype),
-                          (flags & PCF_UPPER_ONLY) != 0, shape_of(flags), plan,
-                          err))
-            return fail(PCF_EINVAL, err);
+        // (a workspace sized for the tile plan keeps it)
+        for (int cus = device_cus();; cus = 0) {
+            if (!plan_batched(B, set_offsets_host, out_offsets_host, ho, all->n,
+                              rec_bytes_of(all->dtype),
+                              (flags & PCF_UPPER_ONLY) != 0, shape_of(flags), plan,
+                              err, cus))
+                return fail(PCF_EINVAL, err);
+            if (cus == 0 ||
+                plan_workspace_bytes(plan, rec_bytes_of(all->dtype)) <= (int64_t)ws_bytes)
+                break;
+        }
     }
     Call c;
     {
@@ -885,8 +923,10 @@ pcf_status pcf_pairwise_batched(int32_t B, const int64_t *set_offsets_host,
         hk = lp_hkind(p, all->dtype == PCF_F64);
         a.root = (kind == PCF_LP_POW || p == 1.0) ? 0 : (p == 2.0 ? 1 : 2);
     }
-    hipError_t e = launch_forward(all->dtype == PCF_F64, hk, a,
-                                  tile_grid(reuse ? nullptr : &plan, reuse), s);
+    hipError_t e = c.strips.waves > 0
+                       ? launch_strips(all->dtype == PCF_F64, hk, a, c.strips, s)
+                       : launch_forward(all->dtype == PCF_F64, hk, a,
+                                        tile_grid(reuse ? nullptr : &plan, reuse), s);
     if (e != hipSuccess)
         return hip_fail(e, "tile kernel launch");
     return PCF_OK;
@@ -1052,7 +1092,7 @@ pcf_status pcf_cross_workspace_bytes(const pcf_set *X, const pcf_set *Y,
     }
     std::vector<int64_t> comb;
     Plan plan;
-    st = cross_plan(X, Y, Y->n, 0, nullptr, comb, plan);
+    st = cross_plan(X, Y, Y->n, 0, nullptr, comb, plan, 0);
     if (st != PCF_OK)
         return st;
     *bytes = (size_t)(cross_offsets_at(plan, rec_bytes_of(X->dtype), true) +
@@ -1083,12 +1123,18 @@ pcf_status pcf_cross(const pcf_set *X, const pcf_set *Y, pcf_kind kind, double p
     hipStream_t s = (hipStream_t)stream;
     std::vector<int64_t> comb;
     Plan plan;
-    st = cross_plan(X, Y, ldo, flags, s, comb, plan);
-    if (st != PCF_OK)
-        return st;
     const int rb = rec_bytes_of(X->dtype);
-    const int64_t at = cross_offsets_at(plan, rb, false);
-    const int64_t need = at + align_up((X->n + Y->n + 1) * 8, 256);
+    int64_t at = 0, need = 0;
+    // (a workspace sized for the tile plan keeps it)
+    for (int cus = device_cus();; cus = 0) {
+        st = cross_plan(X, Y, ldo, flags, s, comb, plan, cus);
+        if (st != PCF_OK)
+            return st;
+        at = cross_offsets_at(plan, rb, false);
+        need = at + align_up((X->n + Y->n + 1) * 8, 256);
+        if (cus == 0 || need <= (int64_t)ws_bytes)
+            break;
+    }
     if ((int64_t)ws_bytes < need)
         return fail(PCF_ENOMEM, "workspace too small: need " + std::to_string(need) +
                                     " bytes, got " + std::to_string(ws_bytes));
@@ -1146,7 +1192,10 @@ pcf_status pcf_cross(const pcf_set *X, const pcf_set *Y, pcf_kind kind, double p
         hk = lp_hkind(p, X->dtype == PCF_F64);
         a.root = (kind == PCF_LP_POW || p == 1.0) ? 0 : (p == 2.0 ? 1 : 2);
     }
-    e = launch_forward(X->dtype == PCF_F64, hk, a, tile_grid(&plan, false), s);
+    const StripLaunch strips = strip_launch(plan, rb);
+    e = strips.waves > 0
+            ? launch_strips(X->dtype == PCF_F64, hk, a, strips, s)
+            : launch_forward(X->dtype == PCF_F64, hk, a, tile_grid(&plan, false), s);
     if (e != hipSuccess)
         return hip_fail(e, "tile kernel launch");
     return PCF_OK;

@@ -60,6 +60,41 @@ constexpr int64_t kMaxRows = (int64_t)1 << 30;
 // Number of hardware XCDs (each with its own L2) on MI355X.
 constexpr int kXcds = 8;
 
+// The strip kernel (strips.hip): row blocks of at most kStripMaxRows PCFs,
+// groups of at most kStripMaxCols columns, at most kStripMaxPairs pairs an
+// item, at most kStripMaxWaves waves a workgroup.
+constexpr int kStripMaxRows = 64;
+constexpr int kStripMaxCols = 32;
+constexpr int kStripMaxPairs = 256;
+constexpr int kStripMaxWaves = 16;
+// Records a thread loads ahead into registers: of its next group, and of its
+// next job's rows.
+constexpr int kStripAhead = 4, kStripRowAhead = 4;
+constexpr int kStripLdsBytes = 160 * 1024;
+constexpr int kStripSharedBytes = 1024;  // job descriptors, row metadata
+// LDS bytes of a wave's partial sums (one slot per pair and lane, see part
+// in tile.hpp), pair table (16 bytes a pair) and column metadata.
+constexpr int strip_wave_bytes(int pairs, int cols)
+{
+    return (pairs + 64 + 1) / 2 * 16 + 16 * pairs + (4 * 2 * cols + 15) / 16 * 16;
+}
+// One column group: its first PCF, its records and its place in the ring's
+// record stream (strips.hip). A sentinel entry ends the table.
+struct StripGroup {
+    int32_t start, rec0;  // first PCF, its first record
+    int32_t size;         // records + (columns << kStripColShift)
+    uint32_t virt;
+};
+constexpr int kStripColShift = 24;  // (a group's records fit LDS)
+// A row block: its first PCF, rows, first record and records.
+struct StripBlock {
+    int32_t lo, rows, rec0, recs;
+};
+// One job: a row block against the column groups [g0, g1).
+struct StripJob {
+    int32_t seg, block, g0, g1;
+};
+
 enum SegType : int32_t { kSegTriangle = 0, kSegRect = 1 };
 
 // A run of tiles sharing one output mapping. Triangle: all block pairs
@@ -73,6 +108,8 @@ struct Segment {
     int32_t b0, b1, c0, c1;
     int32_t type;
     int32_t mirror;      // 1: also write the transposed entry
+    int32_t swap;        // strips: 1: row blocks are columns of the output
+    int32_t reserved;
 };
 
 // Head of the device workspace. Written by the host planner (copied in
@@ -96,7 +133,11 @@ struct WsHeader {
     unsigned long long adj_max[3];
     int64_t off_acc;      // FP32 adjoint plans: 64-bit sums of dL/dt, dL/dv (2 x 8 bytes
                           // a row) for PCF_DETERMINISTIC; else 0
-    int64_t reserved[1];
+    // strip plans: column groups, jobs, and the first job of each of the
+    // ntiles runs of jobs (and the number of jobs)
+    int64_t off_groups, off_jobs, off_runs, off_sblocks;
+    int32_t strip_row_recs, strip_ring_recs;  // records of the row area and the ring
+    int32_t strip_pairs, strip_cols;          // most pairs an item, columns a group
 };
 static_assert(sizeof(WsHeader) <= 256, "header must fit its slot");
 

@@ -21,7 +21,8 @@
 //    first. Both orders give the same cells of positive width, and a lane's
 //    share starts after a whole number of merged breakpoints, whose last
 //    time does not depend on the order, so the shares fit together.
-//  * Tiles and LDS. A workgroup takes a tile (row block x column block) from
+//  * Tiles and LDS (launches that strips.hip does not serve better, see
+//    strips_pay in plan.cpp, and PCFs too long for LDS). A workgroup takes a tile (row block x column block) from
 //    a persistent queue, copies both blocks' records into LDS and splits the
 //    tile's total step count over its 1024 lanes, one contiguous run of
 //    steps per lane, longer runs for the waves the SIMDs issue first (see

@@ -98,6 +98,12 @@ hipError_t launch_apply_root(bool f64, void *out, int64_t rows, int64_t cols, in
 hipError_t launch_reset(unsigned char *ws, hipStream_t s);
 hipError_t launch_forward(bool f64, int hk, const FwdArgs &a, int grid,
                           hipStream_t s);
+// The strip kernel's launch: waves a workgroup, its LDS bytes, workgroups.
+struct StripLaunch {
+    int waves = 0, lds_bytes = 0, grid = 0;
+};
+hipError_t launch_strips(bool f64, int hk, const FwdArgs &a, const StripLaunch &l,
+                         hipStream_t s);
 hipError_t launch_backward(int hk, bool f64, const BwdArgs &a, int grid, hipStream_t s);
 // Deterministic adjoint: the set's largest pair weight, |v| and piece length
 // into the workspace header (before launch_backward with a.fixed), and the

@@ -28,7 +28,7 @@ pcf_status noalloc_forward(const pcf_set *X, pcf_kind kind, double p, void *out,
                            int64_t ldo, const pcf_window *w, void *ws,
                            size_t ws_bytes, uint32_t flags, void *stream);
 pcf_status noalloc_plan_bytes(const pcf_set *X, const pcf_window *w, int64_t ldo,
-                              uint32_t flags, int64_t *bytes);
+                              uint32_t flags, int64_t *bytes, bool bound = false);
 }  // namespace pcf
 
 using namespace pcf;

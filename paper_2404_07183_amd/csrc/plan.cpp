@@ -2,6 +2,7 @@
 #include "plan.hpp"
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 
 namespace pcf {
@@ -87,6 +88,267 @@ bool check_offsets(int64_t n, const int64_t *offsets, std::string &err)
     return true;
 }
 
+// A rectangle or triangle of the matrix with one output mapping: PCF rows
+// [ra, rb) against columns [ca, cb) (triangle: of [ra, rb) with itself).
+struct Region {
+    int64_t ra, rb, ca, cb;
+    Segment map;  // type, mirror and the output mapping
+};
+
+double region_pairs(const Region &g)
+{
+    const double m = (double)(g.rb - g.ra);
+    return g.map.type == kSegTriangle ? 0.5 * m * (m + 1) : m * (double)(g.cb - g.ca);
+}
+
+// Strip plans (strips.hip): waves a workgroup (16 beat 12 by 3 to 20 % and 8
+// by 25 % and more: fewer hide less of each other's latency); ring records
+// over the records in flight (less makes waves wait for the oldest group,
+// more takes rows from the row blocks; FP32 records leave room for more); the
+// share of the work left that goes into the next run of every CU (the XCDs
+// differ by up to 15 % in speed, so the first runs must leave enough to even
+// that out); the fewest items a wave in a run; an item's and a job's cost
+// beside the merge, in steps of a wave.
+constexpr int kStripWaves = 16;
+constexpr double kRunShare = 0.55, kRunLeast = 2.0, kItemSteps = 16.0, kJobSteps = 40.0;
+constexpr double strip_ring(int rec_bytes, int64_t mean)
+{
+    return rec_bytes == 16 || mean > 400 ? 1.25 : 1.45;
+}
+
+// Whether a strip plan is the faster one, for PCFs of `mean` rows and K steps
+// for every lane of the chip. Measured on MI355X (L1, tile kernel / strip
+// kernel, us; row counts uniform around the mean):
+//   FP64 rows  25: K 300 122 / 100   K 3000 1014 / 576   K 40000 12420 / 6435
+//   FP64 rows 200: K 1000 180 / 195  K 3000  480 / 474   K 40000  5929 / 5125
+//   FP64 rows 400: K 1000 253 / 232  K 3000  731 / 579   K 40000  9093 / 6400
+//   FP32 rows  50: K 300  78 /  73   K 3000  656 / 374   K 40000  8331 / 3661
+//   FP32 rows 200: K 1000 134 / 145  K 3000  322 / 335   K 40000  3510 / 3090
+//   FP32 rows 800: K 1000 153 / 188  K 3000  430 / 414   K 40000  5031 / 4527
+// Tiles of short PCFs are bounded by their PCF count and fill LDS badly;
+// elsewhere a strip's jobs must outweigh their starts and ends.
+// `spread` is the mean square of the row counts over their squared mean:
+// columns of very different lengths make waves wait for the oldest one's place
+// in the ring (128 problems of geometric row counts, spread 2: 2350 / 2500).
+bool strips_pay(double mean, double spread, double K, int rec_bytes)
+{
+    if (mean <= 64.0)
+        return K >= 200.0;
+    if (spread > 1.6)
+        return false;
+    if (rec_bytes == 16)
+        return K >= (mean >= 600.0 ? 300.0 : (mean >= 300.0 ? 800.0 : 3000.0));
+    return K >= (mean >= 600.0 ? 3000.0 : 16000.0);
+}
+
+// Strip plan of the regions over PCFs [lo, hi); false where the tile plan is
+// the better one or a PCF is too long for LDS beside the others.
+bool build_strips(const int64_t *offsets, int64_t lo, int64_t hi,
+                  const std::vector<int64_t> &cuts, std::vector<Region> regions,
+                  int rec_bytes, const TileShape &shape, int cus, Plan &plan)
+{
+    int64_t longest = 0;
+    double squares = 0.0;
+    for (int64_t i = lo; i < hi; ++i) {
+        const int64_t r = offsets[i + 1] - offsets[i];
+        longest = std::max(longest, r + kPad);
+        squares += (double)r * (double)r;
+    }
+    const int64_t recs = offsets[hi] - offsets[lo] + (hi - lo) * kPad;
+    const int64_t mean = (recs + (hi - lo) - 1) / (hi - lo);
+    double pairs = 0.0;
+    for (const Region &g : regions)
+        pairs += region_pairs(g);
+    // Steps of a lane's run in an item, s. An item costs about kItemSteps
+    // steps of a wave's time beside its merge, and at a job's end a wave waits
+    // for half an item on average: with K steps for every lane of the chip the
+    // time goes with (s + kItemSteps) (K / s + 1/2), smallest at
+    // s = sqrt(2 K kItemSteps).
+    const double mean_steps = 2.0 * (double)(mean - kPad);
+    const double rows = (double)(offsets[hi] - offsets[lo]) / (double)(hi - lo);
+    if (!strips_pay(rows, squares / (double)(hi - lo) / (rows * rows),
+                    pairs * mean_steps / (64.0 * cus * kStripWaves), rec_bytes))
+        return false;
+    int waves = kStripWaves;
+    int64_t R = 0, M = 1, ring = 0, area = 0;
+    for (; waves >= 4; waves -= 4) {  // (fewer waves for long PCFs)
+        const double K = pairs * mean_steps / (64.0 * cus * waves);
+        const double run = std::min({K, std::sqrt(2.0 * K * kItemSteps), 400.0});
+        const double item = std::max(1.0, run * 64.0 / mean_steps);  // pairs
+        int64_t most = shape.max_block >= kMaxBlock ? kStripMaxRows : shape.max_block;
+        most = std::max<int64_t>(1, std::min(most, (int64_t)item));
+        for (M = 1;; ++M) {
+            R = most;
+            for (int it = 0; it < 3; ++it) {  // (the rows a block gets depend on the
+                                              // waves' areas, and they on the rows)
+                const int64_t bytes =
+                    kStripLdsBytes - kStripSharedBytes -
+                    (int64_t)waves * strip_wave_bytes((int)(R * M), (int)M);
+                ring = std::max((int64_t)(strip_ring(rec_bytes, mean) * (double)(waves * M * mean)),
+                                longest + 2 * M * mean);
+                area = bytes / rec_bytes - ring;
+                // (short PCFs among the rows let a block hold more than the
+                // mean)
+                R = std::max<int64_t>(1, std::min(most, area * 13 / 10 / mean));
+            }
+            // (another column only where a full row block is too little work)
+            if (R < kStripMaxRows || (double)(R * (M + 1)) > item + 1.0 ||
+                R * (M + 1) > kStripMaxPairs || M + 1 > kStripMaxCols)
+                break;
+        }
+        if (area >= longest && area >= 4 * mean)
+            break;
+    }
+    if (waves < 4)
+        return false;
+    area = std::min(area, R * longest);
+    if (shape.budget_div > 2)
+        area = std::max(longest, area * 2 / shape.budget_div);
+
+    plan.blocks.clear();
+    build_blocks(offsets, lo, hi, cuts, area, (int32_t)R, plan.blocks);
+    plan.blocks.push_back((int32_t)hi);
+    const int64_t nblk = (int64_t)plan.blocks.size() - 1;
+    // column groups: at most M PCFs, within one block, at their ring places
+    const int64_t most_recs = std::max(longest, M * mean * 5 / 4);
+    std::vector<int32_t> gfirst((size_t)nblk + 1);
+    plan.groups.clear();
+    uint32_t virt = 0;
+    int64_t at = 0;  // virt modulo the ring
+    auto place = [&](int64_t start, int64_t cols, int64_t len) {
+        if (at + len > ring) {  // no group crosses the ring's end
+            virt += (uint32_t)(ring - at);
+            at = 0;
+        }
+        plan.groups.push_back({(int32_t)start, (int32_t)(offsets[start] + start * kPad),
+                               (int32_t)(len + (cols << kStripColShift)), virt});
+        virt += (uint32_t)len;
+        at += len;
+    };
+    for (int64_t b = 0; b < nblk; ++b) {
+        gfirst[(size_t)b] = (int32_t)plan.groups.size();
+        int64_t i = plan.blocks[(size_t)b];
+        const int64_t e = plan.blocks[(size_t)b + 1];
+        plan.sblocks.push_back({(int32_t)i, (int32_t)(e - i), (int32_t)(offsets[i] + i * kPad),
+                                (int32_t)(offsets[e] - offsets[i] + (e - i) * kPad)});
+        while (i < e) {
+            int64_t j = i, len = 0;
+            do {
+                len += offsets[j + 1] - offsets[j] + kPad;
+                ++j;
+            } while (j < e && j - i < M &&
+                     len + offsets[j + 1] - offsets[j] + kPad <= most_recs);
+            place(i, j - i, len);
+            i = j;
+        }
+    }
+    gfirst[(size_t)nblk] = (int32_t)plan.groups.size();
+    plan.groups.push_back({(int32_t)hi, 0, 0, virt});
+
+    plan.strips = true;
+    plan.strip_waves = waves;
+    plan.strip_row_recs = (int32_t)area;
+    plan.strip_ring_recs = (int32_t)ring;
+    plan.strip_pairs = (int32_t)(R * M);
+    plan.strip_cols = (int32_t)M;
+    // Runs of equal cost: the (row block, group) items of all regions in
+    // order, cut into runs (a workgroup's work between two tickets). One run a
+    // CU unless the launch is long (then the queue evens out what the cost
+    // misses); a run that crosses row blocks holds several jobs.
+    // (a block's cost over groups [g0, g1) by prefix sums of group records)
+    std::vector<double> gcost(plan.groups.size());
+    auto range_cost = [&](int64_t rows, int64_t rowrows, int64_t g0, int64_t g1) {
+        const double m = (double)(plan.groups[(size_t)g1].start - plan.groups[(size_t)g0].start);
+        return (double)(g1 - g0) * kItemSteps +
+               ((double)rows * (gcost[(size_t)g1] - gcost[(size_t)g0]) + m * (double)rowrows) /
+                   64.0;
+    };
+    gcost[0] = 0.0;
+    for (size_t g = 0; g + 1 < plan.groups.size(); ++g)
+        gcost[g + 1] = gcost[g] + (double)(offsets[plan.groups[g + 1].start] -
+                                           offsets[plan.groups[g].start]);
+    double total = 0.0, items = 0.0;
+    for (Region &g : regions) {
+        if (g.map.type == kSegRect && g.rb - g.ra > g.cb - g.ca) {
+            // the longer side streams
+            std::swap(g.ra, g.ca);
+            std::swap(g.rb, g.cb);
+            g.map.swap = 1;
+        }
+        Segment s = g.map;
+        s.b0 = block_at(plan.blocks, g.ra);
+        s.b1 = block_at(plan.blocks, g.rb);
+        s.c0 = block_at(plan.blocks, g.ca);
+        s.c1 = block_at(plan.blocks, g.cb);
+        plan.segs.push_back(s);
+        for (int32_t b = s.b0; b < s.b1; ++b) {
+            const int64_t lo_ = plan.blocks[(size_t)b], hi_ = plan.blocks[(size_t)b + 1];
+            const int64_t g0 = gfirst[(size_t)(s.type == kSegTriangle ? b : s.c0)];
+            total += kJobSteps * waves +
+                     range_cost(hi_ - lo_, offsets[hi_] - offsets[lo_], g0,
+                                gfirst[(size_t)s.c1]);
+            items += (double)(gfirst[(size_t)s.c1] - g0);
+        }
+    }
+    // a run for every CU from a share of what is left, then again: few long
+    // runs first, short ones last
+    const double least = std::min(total / items * kRunLeast * waves, total / cus);
+    double left = total, target = 0.0;
+    int batch = 0;
+    auto next_target = [&]() {
+        if (batch == 0) {
+            target = std::max(least, left * kRunShare / cus);
+            batch = cus;
+        }
+        --batch;
+    };
+    next_target();
+    double used = 0.0;  // cost of the current run so far
+    plan.runs.push_back(0);
+    for (size_t q = 0; q < plan.segs.size(); ++q) {
+        const Segment &s = plan.segs[q];
+        const int64_t gend = gfirst[(size_t)s.c1];
+        for (int32_t b = s.b0; b < s.b1; ++b) {
+            const int64_t rows = plan.blocks[(size_t)b + 1] - plan.blocks[(size_t)b];
+            const int64_t rowrows = offsets[plan.blocks[(size_t)b + 1]] -
+                                    offsets[plan.blocks[(size_t)b]];
+            int64_t g0 = gfirst[(size_t)(s.type == kSegTriangle ? b : s.c0)];
+            while (g0 < gend) {
+                // the groups that fit the run (records of a job's columns stay
+                // below 2^28, see busy in strips.hip)
+                const double room = target - used - kJobSteps * waves;
+                int64_t lo_ = g0 + 1, hi_ = gend;
+                while (lo_ < hi_) {  // most groups within the room
+                    const int64_t mid = (lo_ + hi_ + 1) / 2;
+                    if (range_cost(rows, rowrows, g0, mid) <= room &&
+                        plan.groups[(size_t)mid].virt - plan.groups[(size_t)g0].virt <
+                            (1u << 28))
+                        lo_ = mid;
+                    else
+                        hi_ = mid - 1;
+                }
+                // (a few items left of the row block stay with it)
+                if (gend - lo_ < waves &&
+                    plan.groups[(size_t)gend].virt - plan.groups[(size_t)g0].virt < (1u << 28))
+                    lo_ = gend;
+                plan.jobs.push_back({(int32_t)q, b, (int32_t)g0, (int32_t)lo_});
+                used += kJobSteps * waves + range_cost(rows, rowrows, g0, lo_);
+                g0 = lo_;
+                if (used >= 0.9 * target) {
+                    plan.runs.push_back((int32_t)plan.jobs.size());
+                    left -= used;
+                    used = 0.0;
+                    next_target();
+                }
+            }
+        }
+    }
+    if (plan.runs.back() != (int32_t)plan.jobs.size())
+        plan.runs.push_back((int32_t)plan.jobs.size());
+    plan.ntiles = (int64_t)plan.runs.size() - 1;
+    return true;
+}
+
 void add_segment(Plan &plan, Segment s, int64_t tiles)
 {
     if (tiles <= 0)
@@ -101,7 +363,8 @@ void add_segment(Plan &plan, Segment s, int64_t tiles)
 bool plan_matrix(int64_t n, const int64_t *offsets, int rec_bytes,
                  bool backward, bool windowed, int64_t r0, int64_t r1,
                  int64_t c0, int64_t c1, bool upper_only, int64_t ldo,
-                 const TileShape &shape, Plan &plan, std::string &err)
+                 const TileShape &shape, Plan &plan, std::string &err,
+                 int cus)
 {
     plan = Plan();
     if (!check_offsets(n, offsets, err))
@@ -135,42 +398,28 @@ bool plan_matrix(int64_t n, const int64_t *offsets, int rec_bytes,
         cuts.push_back(d0);
         cuts.push_back(d1);
     }
-    build_blocks(offsets, lo, hi, cuts, block_budget(rec_bytes, backward, shape),
-                 shape.max_block, plan.blocks);
-    plan.blocks.push_back((int32_t)hi);
-
+    // the window's parts: the triangle of its symmetric part; rows outside
+    // the overlap against every column; overlap rows against columns outside
+    // it (the transposes of these entries lie outside the window, so nothing
+    // is mirrored)
+    std::vector<Region> regions;
     Segment base{};
     base.obase = 0;
     base.ldo = ldo;
     base.row0 = r0;
     base.col0 = c0;
-
     auto rect = [&](int64_t ra, int64_t rb, int64_t ca, int64_t cb) {
         if (ra >= rb || ca >= cb)
             return;
         Segment s = base;
         s.type = kSegRect;
-        s.mirror = 0;
-        s.b0 = block_at(plan.blocks, ra);
-        s.b1 = block_at(plan.blocks, rb);
-        s.c0 = block_at(plan.blocks, ca);
-        s.c1 = block_at(plan.blocks, cb);
-        add_segment(plan, s, (int64_t)(s.b1 - s.b0) * (s.c1 - s.c0));
+        regions.push_back({ra, rb, ca, cb, s});
     };
-
     if (has_d) {
         Segment s = base;
         s.type = kSegTriangle;
         s.mirror = upper_only ? 0 : 1;
-        s.b0 = block_at(plan.blocks, d0);
-        s.b1 = block_at(plan.blocks, d1);
-        s.c0 = s.b0;
-        s.c1 = s.b1;
-        const int64_t nb = s.b1 - s.b0;
-        add_segment(plan, s, nb * (nb + 1) / 2);
-        // rows outside the overlap against every column; overlap rows
-        // against columns outside it (the transposes of these entries lie
-        // outside the window, so nothing is mirrored)
+        regions.push_back({d0, d1, d0, d1, s});
         rect(r0, std::min(r1, d0), c0, c1);
         rect(std::max(r0, d1), r1, c0, c1);
         rect(d0, d1, c0, std::min(c1, d0));
@@ -178,13 +427,31 @@ bool plan_matrix(int64_t n, const int64_t *offsets, int rec_bytes,
     } else {
         rect(r0, r1, c0, c1);
     }
+    if (cus > 0 && !backward &&
+        build_strips(offsets, lo, hi, cuts, regions, rec_bytes, shape, cus, plan))
+        return true;
+
+    build_blocks(offsets, lo, hi, cuts, block_budget(rec_bytes, backward, shape),
+                 shape.max_block, plan.blocks);
+    plan.blocks.push_back((int32_t)hi);
+    for (const Region &g : regions) {
+        Segment s = g.map;
+        s.b0 = block_at(plan.blocks, g.ra);
+        s.b1 = block_at(plan.blocks, g.rb);
+        s.c0 = block_at(plan.blocks, g.ca);
+        s.c1 = block_at(plan.blocks, g.cb);
+        const int64_t nb = s.b1 - s.b0;
+        add_segment(plan, s,
+                    s.type == kSegTriangle ? nb * (nb + 1) / 2 : nb * (s.c1 - s.c0));
+    }
     return true;
 }
 
 bool plan_batched(int32_t B, const int64_t *set_offsets,
                   const int64_t *out_offsets, const int64_t *offsets,
                   int64_t n, int rec_bytes, bool upper_only,
-                  const TileShape &shape, Plan &plan, std::string &err)
+                  const TileShape &shape, Plan &plan, std::string &err,
+                  int cus)
 {
     plan = Plan();
     if (B < 0 || (B > 0 && (!set_offsets || !out_offsets))) {
@@ -211,14 +478,9 @@ bool plan_batched(int32_t B, const int64_t *set_offsets,
         return true;
     const int64_t lo = set_offsets[0], hi = set_offsets[B];
     std::vector<int64_t> cuts(set_offsets, set_offsets + B + 1);
-    build_blocks(offsets, lo, hi, cuts, block_budget(rec_bytes, false, shape),
-                 shape.max_block, plan.blocks);
-    plan.blocks.push_back((int32_t)hi);
-
     struct Item {
         double cost;
-        Segment s;
-        int64_t tiles;
+        Region g;
     };
     std::vector<Item> items;
     for (int32_t b = 0; b < B; ++b) {
@@ -231,21 +493,33 @@ bool plan_batched(int32_t B, const int64_t *set_offsets,
         s.obase = out_offsets[b];
         s.ldo = e - a;
         s.row0 = s.col0 = a;
-        s.b0 = block_at(plan.blocks, a);
-        s.b1 = block_at(plan.blocks, e);
-        s.c0 = s.b0;
-        s.c1 = s.b1;
-        const int64_t nb = s.b1 - s.b0;
         // merge steps of a set of s PCFs with R rows in total: about
         // s * R (every PCF meets every other once)
         const double cost =
             (double)(e - a) * (double)(offsets[e] - offsets[a]);
-        items.push_back({cost, s, nb * (nb + 1) / 2});
+        items.push_back({cost, {a, e, a, e, s}});
     }
     std::stable_sort(items.begin(), items.end(),
                      [](const Item &x, const Item &y) { return x.cost > y.cost; });
-    for (auto &it : items)
-        add_segment(plan, it.s, it.tiles);
+    if (items.empty())
+        return true;
+    if (cus > 0) {
+        std::vector<Region> regions;
+        for (auto &it : items)
+            regions.push_back(it.g);
+        if (build_strips(offsets, lo, hi, cuts, regions, rec_bytes, shape, cus, plan))
+            return true;
+    }
+    build_blocks(offsets, lo, hi, cuts, block_budget(rec_bytes, false, shape),
+                 shape.max_block, plan.blocks);
+    plan.blocks.push_back((int32_t)hi);
+    for (auto &it : items) {
+        Segment s = it.g.map;
+        s.b0 = s.c0 = block_at(plan.blocks, it.g.ra);
+        s.b1 = s.c1 = block_at(plan.blocks, it.g.rb);
+        const int64_t nb = s.b1 - s.b0;
+        add_segment(plan, s, nb * (nb + 1) / 2);
+    }
     return true;
 }
 
@@ -264,6 +538,10 @@ int64_t plan_workspace_bytes(const Plan &plan, int rec_bytes)
     int64_t off = kHeaderBytes;
     off += align_up((int64_t)plan.blocks.size() * 4, 256);
     off += align_up((int64_t)plan.segs.size() * (int64_t)sizeof(Segment), 256);
+    off += align_up((int64_t)plan.groups.size() * (int64_t)sizeof(StripGroup), 256);
+    off += align_up((int64_t)plan.jobs.size() * (int64_t)sizeof(StripJob), 256);
+    off += align_up((int64_t)plan.runs.size() * 4, 256);
+    off += align_up((int64_t)plan.sblocks.size() * (int64_t)sizeof(StripBlock), 256);
     off += align_up(plan.rec_count * rec_bytes, 256);
     off += adj_acc_bytes(plan, rec_bytes);
     return off;
@@ -276,6 +554,14 @@ int64_t plan_workspace_bound(const Plan &plan, int rec_bytes)
     off += align_up((int64_t)plan.segs.size() * (int64_t)sizeof(Segment), 256);
     off += align_up(plan.rec_count * rec_bytes, 256);
     off += adj_acc_bytes(plan, rec_bytes);
+    if (!plan.backward) {
+        // a strip plan's groups and jobs (at most one job a row block of each
+        // of a window's parts beside the division by size)
+        off += align_up((plan.npcf + 2) * (int64_t)sizeof(StripGroup), 256);
+        off += align_up((plan.npcf + 2) * (int64_t)sizeof(StripBlock), 256);
+        off += align_up((3 * plan.npcf + 16384) * (int64_t)sizeof(StripJob), 256);
+        off += align_up(16384 * 4, 256);
+    }
     return off;
 }
 
@@ -289,8 +575,19 @@ void plan_serialise(const Plan &plan, int rec_bytes,
     hdr.npcf = plan.npcf;
     hdr.off_blocks = kHeaderBytes;
     hdr.off_segs = hdr.off_blocks + align_up((int64_t)plan.blocks.size() * 4, 256);
-    hdr.off_rec = hdr.off_segs +
-                  align_up((int64_t)plan.segs.size() * (int64_t)sizeof(Segment), 256);
+    hdr.off_groups = hdr.off_segs +
+                     align_up((int64_t)plan.segs.size() * (int64_t)sizeof(Segment), 256);
+    hdr.off_jobs = hdr.off_groups +
+                   align_up((int64_t)plan.groups.size() * (int64_t)sizeof(StripGroup), 256);
+    hdr.off_runs = hdr.off_jobs +
+                   align_up((int64_t)plan.jobs.size() * (int64_t)sizeof(StripJob), 256);
+    hdr.off_sblocks = hdr.off_runs + align_up((int64_t)plan.runs.size() * 4, 256);
+    hdr.off_rec = hdr.off_sblocks +
+                  align_up((int64_t)plan.sblocks.size() * (int64_t)sizeof(StripBlock), 256);
+    hdr.strip_row_recs = plan.strip_row_recs;
+    hdr.strip_ring_recs = plan.strip_ring_recs;
+    hdr.strip_pairs = plan.strip_pairs;
+    hdr.strip_cols = plan.strip_cols;
     hdr.rec_count = plan.rec_count;
     hdr.rec_bytes = rec_bytes;
     hdr.first_bad = -1;
@@ -306,6 +603,17 @@ void plan_serialise(const Plan &plan, int rec_bytes,
     if (!plan.segs.empty())
         std::memcpy(buf.data() + hdr.off_segs, plan.segs.data(),
                     plan.segs.size() * sizeof(Segment));
+    if (!plan.groups.empty())
+        std::memcpy(buf.data() + hdr.off_groups, plan.groups.data(),
+                    plan.groups.size() * sizeof(StripGroup));
+    if (!plan.jobs.empty())
+        std::memcpy(buf.data() + hdr.off_jobs, plan.jobs.data(),
+                    plan.jobs.size() * sizeof(StripJob));
+    if (!plan.runs.empty())
+        std::memcpy(buf.data() + hdr.off_runs, plan.runs.data(), plan.runs.size() * 4);
+    if (!plan.sblocks.empty())
+        std::memcpy(buf.data() + hdr.off_sblocks, plan.sblocks.data(),
+                    plan.sblocks.size() * sizeof(StripBlock));
 }
 
 }  // namespace pcf

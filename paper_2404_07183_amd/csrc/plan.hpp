@@ -7,6 +7,9 @@
 // a block of its own and its tiles read records from global memory. Only the
 // upper triangle of each symmetric part is tiled; the transposed entries are
 // written from the same result (F is symmetric because h is).
+//
+// A strip plan (strips.hip) cuts the same parts into jobs instead: a row block
+// that stays in LDS against a run of column groups that stream through it.
 #pragma once
 
 #include <stdint.h>
@@ -26,6 +29,14 @@ struct Plan {
     int64_t rec_count = 0;        // offsets[n] + n * kPad
     int64_t lds_records = 0;
     bool backward = false;        // an adjoint plan
+    // strip plans (strips.hip): ntiles runs of jobs; blocks are the row blocks
+    bool strips = false;
+    std::vector<StripGroup> groups;
+    std::vector<StripBlock> sblocks;  // (blocks again, with their records)
+    std::vector<StripJob> jobs;
+    std::vector<int32_t> runs;  // first job of each run, and the number of jobs
+    int32_t strip_waves = 0, strip_row_recs = 0, strip_ring_recs = 0;
+    int32_t strip_pairs = 0, strip_cols = 0;
 };
 
 // Tile shape: at most `max_block` PCFs per block and at most 1/`budget_div`
@@ -47,17 +58,21 @@ void build_blocks(const int64_t *offsets, int64_t lo, int64_t hi,
                   std::vector<int32_t> &blocks);
 
 // Plan for one n x n matrix, or the window [r0,r1) x [c0,c1) of it.
-// Returns false with a message in `err` on bad input.
+// Returns false with a message in `err` on bad input. With cus > 0 (the
+// device's CUs) a forward plan is a strip plan where that pays (build_strips),
+// else, and always with 0, a tile plan.
 bool plan_matrix(int64_t n, const int64_t *offsets, int rec_bytes,
                  bool backward, bool windowed, int64_t r0, int64_t r1,
                  int64_t c0, int64_t c1, bool upper_only, int64_t ldo,
-                 const TileShape &shape, Plan &plan, std::string &err);
+                 const TileShape &shape, Plan &plan, std::string &err,
+                 int cus = 0);
 
 // Plan for B independent full matrices in one launch.
 bool plan_batched(int32_t B, const int64_t *set_offsets,
                   const int64_t *out_offsets, const int64_t *offsets,
                   int64_t n, int rec_bytes, bool upper_only,
-                  const TileShape &shape, Plan &plan, std::string &err);
+                  const TileShape &shape, Plan &plan, std::string &err,
+                  int cus = 0);
 
 // Bytes of workspace a plan needs (header, blocks, segments, records).
 // Bytes of an FP32 adjoint plan's 64-bit gradient sums (0 otherwise).
