@@ -213,6 +213,10 @@ pcf_status check_reused_plan(const void *ws, const PlanTag &tag, StripLaunch &st
     return PCF_OK;
 }
 
+// The largest plan written by kernel arguments (three launches; a copy and the
+// wait for it take as long as that).
+constexpr size_t kArgPlanBytes = 3 * sizeof(PlanChunk);
+
 // Copy a plan's header, blocks and segments into the workspace.
 pcf_status upload_plan(const Plan &plan, int rec_bytes, void *ws,
                        size_t ws_bytes, hipStream_t s, const PlanTag &tag)
@@ -228,10 +232,14 @@ pcf_status upload_plan(const Plan &plan, int rec_bytes, void *ws,
     std::vector<unsigned char> buf;
     WsHeader hdr;
     plan_serialise(plan, rec_bytes, buf, hdr);
-    hipError_t e = hipMemcpyAsync(ws, buf.data(), buf.size(),
-                                  hipMemcpyHostToDevice, s);
-    if (e == hipSuccess)
-        e = hipStreamSynchronize(s);  // buf is a local
+    hipError_t e;
+    if (buf.size() <= kArgPlanBytes) {
+        e = launch_write_plan((unsigned char *)ws, buf.data(), (int64_t)buf.size(), s);
+    } else {
+        e = hipMemcpyAsync(ws, buf.data(), buf.size(), hipMemcpyHostToDevice, s);
+        if (e == hipSuccess)
+            e = hipStreamSynchronize(s);  // buf is a local
+    }
     if (e != hipSuccess)
         return hip_fail(e, "uploading the tile plan");
     remember_plan(ws, tag, strip_launch(plan, rec_bytes));
@@ -304,13 +312,14 @@ pcf_status prepare(const pcf_set *X, const Plan *plan, void *ws,
     if ((flags & PCF_RECORDS_PACKED) && !c.reuse)
         return fail(PCF_EINVAL, "PCF_RECORDS_PACKED needs PCF_REUSE_PLAN");
     unsigned char *w = (unsigned char *)ws;
-    hipError_t e = launch_reset(w, s);
-    if (e == hipSuccess && !(flags & PCF_RECORDS_PACKED)) {
-        // grid-stride; with an unknown row count use a full-chip grid
-        const int64_t P = c.P >= 0 ? c.P : (int64_t)1 << 40;
+    hipError_t e;
+    if (flags & PCF_RECORDS_PACKED) {
+        e = launch_reset(w, s);
+    } else {
+        const int64_t mean = c.P >= 0 ? c.P / X->n : 0;
         e = X->dtype == PCF_F64
-                ? launch_pack<double>(X->offsets, X->n, X->t, X->v, w, P, s)
-                : launch_pack<float>(X->offsets, X->n, X->t, X->v, w, P, s);
+                ? launch_pack<double>(X->offsets, X->n, X->t, X->v, w, mean, s)
+                : launch_pack<float>(X->offsets, X->n, X->t, X->v, w, mean, s);
     }
     if (e != hipSuccess)
         return hip_fail(e, "packing breakpoint records");
@@ -1163,17 +1172,16 @@ pcf_status pcf_cross(const pcf_set *X, const pcf_set *Y, pcf_kind kind, double p
     int64_t *coff = reinterpret_cast<int64_t *>(w + at);
     const int64_t px = comb[X->n], py = comb[X->n + Y->n] - px;
     const int64_t ybase = px + X->n * kPad;
-    hipError_t e = launch_reset(w, s);
-    if (e == hipSuccess)
-        e = launch_concat_offsets(X->offsets, X->n, Y->offsets, Y->n, coff, s);
-    if (e == hipSuccess)
-        e = X->dtype == PCF_F64
-                ? launch_pack<double>(X->offsets, X->n, X->t, X->v, w, px, s, 0)
-                : launch_pack<float>(X->offsets, X->n, X->t, X->v, w, px, s, 0);
+    hipError_t e = launch_concat_offsets(X->offsets, X->n, Y->offsets, Y->n, coff, s);
+    const int64_t mx = px / X->n, my = py / Y->n;
     if (e == hipSuccess)
         e = X->dtype == PCF_F64
-                ? launch_pack<double>(Y->offsets, Y->n, Y->t, Y->v, w, py, s, ybase)
-                : launch_pack<float>(Y->offsets, Y->n, Y->t, Y->v, w, py, s, ybase);
+                ? launch_pack<double>(X->offsets, X->n, X->t, X->v, w, mx, s, 0)
+                : launch_pack<float>(X->offsets, X->n, X->t, X->v, w, mx, s, 0);
+    if (e == hipSuccess)
+        e = X->dtype == PCF_F64
+                ? launch_pack<double>(Y->offsets, Y->n, Y->t, Y->v, w, my, s, ybase)
+                : launch_pack<float>(Y->offsets, Y->n, Y->t, Y->v, w, my, s, ybase);
     if (e != hipSuccess)
         return hip_fail(e, "packing breakpoint records");
 

@@ -48,10 +48,18 @@ struct BwdArgs {
                              // launch_adj_finish (needs launch_adj_bounds first)
 };
 
+// Packs a set's records and resets the tile counters (mean: rows a PCF on
+// average, 0 when not known).
 template <typename T>
 hipError_t launch_pack(const int64_t *offsets, int64_t n, const void *t,
-                       const void *v, unsigned char *ws, int64_t P,
+                       const void *v, unsigned char *ws, int64_t mean,
                        hipStream_t s, int64_t rec_base = 0);
+// A plan's bytes (a multiple of 4) as kernel arguments, a few KiB a launch.
+struct PlanChunk {
+    uint32_t word[896];
+};
+hipError_t launch_write_plan(unsigned char *ws, const unsigned char *plan, int64_t bytes,
+                             hipStream_t s);
 hipError_t launch_concat_offsets(const int64_t *xo, int64_t nx, const int64_t *yo,
                                  int64_t ny, int64_t *out, hipStream_t s);
 template <typename T>
