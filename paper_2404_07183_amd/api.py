@@ -110,6 +110,13 @@ def _flags(upper_only, validate, reuse, shape=None):
     return f
 
 
+def _new_out(shape, X, upper_only):
+    """A new output matrix. A call writes all of its entries; with
+    ``upper_only`` the others are 0."""
+    make = torch.zeros if upper_only else torch.empty
+    return make(shape, dtype=X.dtype, device=X.t.device)
+
+
 def _check_out(out, X, oshape):
     """A caller's output matrix: the input's dtype and device, row-major,
     at least ``oshape`` (the library writes rows of ``oshape[1]`` entries at
@@ -133,7 +140,7 @@ def _forward(X, kind, p, window, out, upper_only, validate, workspace, stream,
     else:
         oshape = (window[1] - window[0], window[3] - window[2])
     if out is None:
-        out = torch.zeros(oshape, dtype=X.dtype, device=X.t.device)
+        out = _new_out(oshape, X, upper_only)
     _check_out(out, X, oshape)
     ldo = out.stride(0) if out.shape[0] > 1 else max(out.shape[1], 1)
     # the plan depends on the record size (dtype) and on the plan type
@@ -200,7 +207,7 @@ def pairwise_terms(X, terms, root=None, *, window=None, out=None, upper_only=Fal
     win = _window(window)
     oshape = (X.n, X.n) if window is None else (window[1] - window[0], window[3] - window[2])
     if out is None:
-        out = torch.zeros(oshape, dtype=X.dtype, device=X.t.device)
+        out = _new_out(oshape, X, upper_only)
     _check_out(out, X, oshape)
     ldo = out.stride(0) if out.shape[0] > 1 else max(out.shape[1], 1)
     ct = []
@@ -226,7 +233,7 @@ def _cross(X, Y, kind, p, out, validate, workspace, stream, shape=None):
     if Y.t.device != X.t.device:
         raise ValueError("X and Y must be on one device")
     if out is None:
-        out = torch.zeros((X.n, Y.n), dtype=X.dtype, device=X.t.device)
+        out = _new_out((X.n, Y.n), X, False)
     _check_out(out, X, (X.n, Y.n))
     ldo = out.stride(0) if out.shape[0] > 1 else max(out.shape[1], 1)
     ws = workspace if workspace is not None else Workspace(device=X.t.device)
@@ -481,7 +488,7 @@ def pairwise_batched(set_offsets, X, kind=PCF_LP, p=1.0, *, out=None, workspace=
         oo[1:] = np.cumsum(sizes[:-1] ** 2)
     total = int((sizes ** 2).sum())
     if out is None:
-        out = torch.zeros(total, dtype=X.dtype, device=X.t.device)
+        out = _new_out(total, X, upper_only)
     if out.dtype != X.dtype or not out.is_contiguous() or out.device != X.t.device:
         raise ValueError("out must be a contiguous tensor of the set's dtype and device")
     if out.numel() < total:
