@@ -6,6 +6,7 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <algorithm>
 #include <limits>
 #include <mutex>
 #include <string>
@@ -507,11 +508,21 @@ pcf_status check_weight(int weight, double c)
 constexpr int64_t kRedChunkRows = 1024;  // the root pass's chunk (reduce.hip)
 constexpr int64_t kRedStdSlots = 64;     // the std pass's bounds per chunk (reduce.hip)
 
+// A pass of the tree over `depth` levels at once: its bundles (at index
+// `bundles` of the plan's meta), samples and tiles (reduce.hip).
+struct RedPass {
+    int level = 0, depth = 0;
+    int64_t bundles = 0, nbundles = 0, nsamples = 0, ntiles = 0;
+};
+
 struct RedPlan {
     int32_t B = 0;
     int L = 0;
     int64_t n = 0, P = 0, C = 0;  // PCFs, rows, chunks
-    std::vector<int64_t> meta;    // groups (B+1), chunk rows (C), chunk groups (C)
+    // groups (B+1), chunk rows (C), chunk groups (C), the fused passes' bundles
+    std::vector<int64_t> meta;
+    std::vector<RedPass> passes;  // none: L single levels (0 or 1)
+    size_t off_split = 0;
     size_t off_ccnt = 0, off_coff = 0, off_buf[4] = {0, 0, 0, 0}, off_q = 0, off_map = 0;
     size_t off_kb = 0;  // PCF_REDUCE_STD: each chunk's first rows (64 per chunk)
     size_t bytes = 0;
@@ -519,8 +530,10 @@ struct RedPlan {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Checks, layout and, with `tables`, the tables (the sizes alone serve the
+// workspace query and the call that writes the rows).
 pcf_status red_plan(const pcf_set *X, int32_t B, const int64_t *groups, int op,
-                    hipStream_t s, RedPlan &rp)
+                    hipStream_t s, RedPlan &rp, bool tables)
 {
     pcf_status st = check_set(X);
     if (st != PCF_OK)
@@ -560,22 +573,64 @@ pcf_status red_plan(const pcf_set *X, int32_t B, const int64_t *groups, int op,
     rp.L = 0;
     while (((int64_t)1 << rp.L) < mmax)
         ++rp.L;
-    if (groups)
-        rp.meta.assign(groups, groups + B + 1);
-    else
-        rp.meta.assign(1, 0);
-    std::vector<int64_t> crow, cgrp;
+    rp.C = 0;
     for (int32_t b = 0; b < B; ++b)
-        for (int64_t r = ho[groups[b]]; r < ho[groups[b + 1]]; r += kRedChunkRows) {
-            crow.push_back(r);
-            cgrp.push_back(b);
+        rp.C += (ho[groups[b + 1]] - ho[groups[b]] + kRedChunkRows - 1) / kRedChunkRows;
+    int64_t entries = (int64_t)B + 1 + 2 * rp.C;
+    // more than one level: passes of up to kFuseLevels levels, evenly
+    const int npass = rp.L > 1 ? (rp.L + kFuseLevels - 1) / kFuseLevels : 0;
+    int64_t most_tiles = 0;  // (a bound from the rows and items)
+    for (int q = 0, level = 0; q < npass; ++q) {
+        RedPass ps;
+        ps.level = level;
+        ps.depth = (rp.L - level + npass - q - 1) / (npass - q);
+        ps.bundles = entries;
+        const int64_t out = (int64_t)1 << (level + ps.depth);
+        int64_t items = 0;
+        for (int32_t b = 0; b < B; ++b) {
+            const int64_t m = groups[b + 1] - groups[b];
+            ps.nbundles += (m + out - 1) / out;
+            items += (m + ((int64_t)1 << level) - 1) >> level;
         }
-    rp.C = (int64_t)crow.size();
-    rp.meta.insert(rp.meta.end(), crow.begin(), crow.end());
-    rp.meta.insert(rp.meta.end(), cgrp.begin(), cgrp.end());
+        entries += 4 * ps.nbundles;
+        most_tiles = std::max(most_tiles, (rp.P / kFuseSpacing + items) / kFuseRanks +
+                                              ps.nbundles);
+        rp.passes.push_back(ps);
+        level += ps.depth;
+    }
+    if (tables) {
+        rp.meta.resize((size_t)entries, 0);
+        int64_t *meta = rp.meta.data();
+        std::copy(groups, groups + (B > 0 ? B + 1 : 0), meta);
+        int64_t *crow = meta + B + 1, *cgrp = crow + rp.C;
+        for (int32_t b = 0; b < B; ++b)
+            for (int64_t r = ho[groups[b]]; r < ho[groups[b + 1]]; r += kRedChunkRows) {
+                *crow++ = r;
+                *cgrp++ = b;
+            }
+        for (RedPass &ps : rp.passes) {
+            const int64_t item = (int64_t)1 << ps.level, out = item << ps.depth;
+            int64_t *to = meta + ps.bundles;
+            for (int32_t b = 0; b < B; ++b)
+                for (int64_t p = groups[b]; p < groups[b + 1]; p += out) {
+                    const int64_t pend = std::min(p + out, groups[b + 1]);
+                    *to++ = p;
+                    *to++ = pend;
+                    *to++ = ps.nsamples;
+                    *to++ = ps.ntiles;
+                    int64_t ns = 0;
+                    for (int64_t i = p; i < pend; i += item)
+                        ns += (int64_t)((uint64_t)(ho[std::min(i + item, pend)] - ho[i] +
+                                                   kFuseSpacing - 1) /
+                                        (uint64_t)kFuseSpacing);
+                    ps.nsamples += ns;
+                    ps.ntiles += (ns + kFuseRanks - 1) / kFuseRanks;
+                }
+        }
+    }
     const size_t esz = X->dtype == PCF_F64 ? 8 : 4;
     const size_t cbytes = align256((size_t)(rp.C > 0 ? rp.C : 1) * sizeof(int64_t));
-    size_t off = align256(rp.meta.size() * sizeof(int64_t));
+    size_t off = align256((size_t)entries * sizeof(int64_t));
     rp.off_ccnt = off;
     off += cbytes;
     rp.off_coff = off;
@@ -586,8 +641,10 @@ pcf_status red_plan(const pcf_set *X, int32_t B, const int64_t *groups, int op,
     }
     rp.off_q = off;
     off += align256((size_t)(rp.P > 0 ? rp.P : 1) * esz);
-    rp.off_map = off;
-    off += align256((size_t)(rp.P > 0 ? rp.P : 1) * sizeof(int32_t));
+    // (the fused passes' splits, or the single level's row map)
+    rp.off_map = rp.off_split = off;
+    off += std::max(align256((size_t)(rp.P > 0 ? rp.P : 1) * sizeof(int32_t)),
+                    align256((size_t)most_tiles * kFuseSplit * sizeof(int64_t)));
     if (op == PCF_REDUCE_STD) {
         rp.off_kb = off;
         off += align256((size_t)(rp.C > 0 ? rp.C : 1) * kRedStdSlots * sizeof(int64_t));
@@ -1382,7 +1439,7 @@ pcf_status pcf_reduce_workspace_bytes(const pcf_set *X, int32_t B,
     if (op < PCF_REDUCE_SUM || op > PCF_REDUCE_STD)
         return fail(PCF_EINVAL, "unknown reduction op");
     RedPlan rp;
-    pcf_status st = red_plan(X, B, group_offsets_host, (int)op, nullptr, rp);
+    pcf_status st = red_plan(X, B, group_offsets_host, (int)op, nullptr, rp, false);
     if (st != PCF_OK)
         return st;
     *bytes = rp.bytes;
@@ -1399,7 +1456,7 @@ void red_roots(const pcf_set *X, const RedPlan &rp, unsigned char *w, const void
         rt = X->t;
         rv = X->v;
     } else {
-        const int k = (rp.L - 1) % 2;
+        const int k = rp.passes.empty() ? 0 : (int)(rp.passes.size() - 1) % 2;
         rt = w + rp.off_buf[2 * k];
         rv = w + rp.off_buf[2 * k + 1];
     }
@@ -1414,7 +1471,7 @@ static pcf_status reduce_rows_impl(const pcf_set *X, int32_t B,
 {
     hipStream_t s = (hipStream_t)stream;
     RedPlan rp;
-    pcf_status st = red_plan(X, B, group_offsets_host, (int)op, s, rp);
+    pcf_status st = red_plan(X, B, group_offsets_host, (int)op, s, rp, true);
     if (st != PCF_OK)
         return st;
     if (!offsets_out || !offsets_out_host)
@@ -1431,23 +1488,41 @@ static pcf_status reduce_rows_impl(const pcf_set *X, int32_t B,
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);  // rp.meta is a local
     const bool f64 = X->dtype == PCF_F64;
-    int32_t *row_pcf = (int32_t *)(w + rp.off_map);
-    if (e == hipSuccess && rp.L > 0)
+    for (size_t q = 0; q < rp.passes.size() && e == hipSuccess; ++q) {
+        const RedPass &ps = rp.passes[q];
+        RedFuseArgs a;
+        a.offsets = X->offsets;
+        a.bundles = (const RedBundle *)(meta + ps.bundles);
+        a.nbundles = ps.nbundles;
+        a.nsamples = ps.nsamples;
+        a.ntiles = ps.ntiles;
+        a.level = ps.level;
+        a.depth = ps.depth;
+        const size_t ki = (q + 1) % 2, ko = q % 2;  // pass q writes buffer pair q % 2
+        a.tin = q == 0 ? X->t : (const void *)(w + rp.off_buf[2 * ki]);
+        a.vin = q == 0 ? X->v : (const void *)(w + rp.off_buf[2 * ki + 1]);
+        a.tout = w + rp.off_buf[2 * ko];
+        a.vout = w + rp.off_buf[2 * ko + 1];
+        a.split = (int64_t *)(w + rp.off_split);
+        e = launch_red_fuse(f64, (int)op, a, s);
+    }
+    if (e == hipSuccess && rp.L == 1) {
+        // one level (and the combinations of two sets): no pass to share
+        int32_t *row_pcf = (int32_t *)(w + rp.off_map);
         e = launch_red_rowmap(X->offsets, rp.n, row_pcf, s);
-    for (int l = 0; l < rp.L && e == hipSuccess; ++l) {
         RedLevelArgs a;
         a.offsets = X->offsets;
         a.groups = meta;
         a.row_pcf = row_pcf;
         a.n = rp.n;
         a.B = B;
-        a.level = l;
-        const int ki = (l + 1) % 2, ko = l % 2;  // level l writes buffer pair l % 2
-        a.tin = l == 0 ? X->t : (const void *)(w + rp.off_buf[2 * ki]);
-        a.vin = l == 0 ? X->v : (const void *)(w + rp.off_buf[2 * ki + 1]);
-        a.tout = w + rp.off_buf[2 * ko];
-        a.vout = w + rp.off_buf[2 * ko + 1];
-        e = launch_red_level(f64, (int)op, a, rp.P, s);
+        a.level = 0;
+        a.tin = X->t;
+        a.vin = X->v;
+        a.tout = w + rp.off_buf[0];
+        a.vout = w + rp.off_buf[1];
+        if (e == hipSuccess)
+            e = launch_red_level(f64, (int)op, a, rp.P, s);
     }
     const void *rt, *rv;
     red_roots(X, rp, w, rt, rv);
@@ -1494,36 +1569,22 @@ static pcf_status reduce_rows_impl(const pcf_set *X, int32_t B,
         a.t_out = a.v_out = nullptr;
         e = launch_red_emit(f64, a, s);
     }
-    std::vector<int64_t> cc((size_t)rp.C);
+    if (e == hipSuccess) {
+        RedScanArgs a;
+        a.nchunks = rp.C;
+        a.B = B;
+        a.chunk_cnt = ccnt;
+        a.chunk_grp = meta + B + 1 + rp.C;
+        a.chunk_off = coff;
+        a.offsets_out = offsets_out;
+        e = launch_red_scan(a, s);
+    }
     if (e == hipSuccess)
-        e = hipMemcpyAsync(cc.data(), ccnt, sizeof(int64_t) * (size_t)rp.C,
+        e = hipMemcpyAsync(offsets_out_host, offsets_out, sizeof(int64_t) * (size_t)(B + 1),
                            hipMemcpyDeviceToHost, s);
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);
-    if (e != hipSuccess)
-        return hip_fail(e, "reduction launch");
-    // chunk counts -> chunk output offsets (chunks are in group order) and
-    // per-group offsets
-    const int64_t *cgrp = rp.meta.data() + B + 1 + rp.C;
-    std::vector<int64_t> gc((size_t)B, 0);
-    int64_t acc = 0;
-    for (int64_t c = 0; c < rp.C; ++c) {
-        const int64_t k = cc[(size_t)c];
-        cc[(size_t)c] = acc;
-        acc += k;
-        gc[(size_t)cgrp[c]] += k;
-    }
-    offsets_out_host[0] = 0;
-    for (int32_t b = 0; b < B; ++b)
-        offsets_out_host[b + 1] = offsets_out_host[b] + gc[(size_t)b];
-    e = hipMemcpyAsync(coff, cc.data(), sizeof(int64_t) * (size_t)rp.C, hipMemcpyHostToDevice,
-                       s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(offsets_out, offsets_out_host, sizeof(int64_t) * (size_t)(B + 1),
-                           hipMemcpyHostToDevice, s);
-    if (e == hipSuccess)
-        e = hipStreamSynchronize(s);  // cc and offsets_out_host may be locals
-    return e == hipSuccess ? PCF_OK : hip_fail(e, "writing the reduced offsets");
+    return e == hipSuccess ? PCF_OK : hip_fail(e, "reduction launch");
 }
 
 static pcf_status reduce_fill_impl(const pcf_set *X, int32_t B,
@@ -1533,7 +1594,7 @@ static pcf_status reduce_fill_impl(const pcf_set *X, int32_t B,
 {
     hipStream_t s = (hipStream_t)stream;
     RedPlan rp;
-    pcf_status st = red_plan(X, B, group_offsets_host, (int)op, s, rp);
+    pcf_status st = red_plan(X, B, group_offsets_host, (int)op, s, rp, false);
     if (st != PCF_OK)
         return st;
     if (B == 0)
@@ -1663,7 +1724,7 @@ pcf_status comb_plan(const pcf_set *X, const pcf_set *Y, int op, unsigned char *
     cp.Z.dtype = X->dtype;
     cp.Z.offsets_host = cp.zoff.data();
     if (n > 0) {
-        st = red_plan(&cp.Z, (int32_t)n, cp.groups.data(), cp.ro, s, cp.rp);
+        st = red_plan(&cp.Z, (int32_t)n, cp.groups.data(), cp.ro, s, cp.rp, false);
         if (st != PCF_OK)
             return st;
     }

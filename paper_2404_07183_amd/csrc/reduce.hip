@@ -8,7 +8,8 @@
 // Tree. A group of M PCFs is reduced by a binary tree: at level l the items
 // 2j and 2j+1 (each covering 2^l consecutive PCFs) are merged into item j of
 // level l+1, and an unpaired last item moves up unchanged. Every group takes
-// the same ceil(log2 M_max) levels, one launch per level for all groups.
+// the same ceil(log2 M_max) levels, up to four of them in one pass for all
+// groups (red_fuse); a tree of one level takes red_level.
 //
 // Merge without compaction. A level keeps every position of the merged
 // breakpoint lists (ties: the first list first), so item j of level l+1
@@ -17,15 +18,15 @@
 // with time x carries h(f(x), g(x)): a list's value at x is its next row's
 // when that row also lies at x (all rows at one time carry the same value,
 // by induction from the strictly increasing inputs), else its last row's.
-// Positions are independent given the merge state, so one launch per level
-// covers all rows of all pairs: a lane walks kMergeK consecutive rows after
-// a merge-path search, moving on to the next pair in place when it crosses
-// one. ReducePair's row rule (keep t = 0 and value changes) is applied once,
+// Positions are independent given the merge state, so one launch covers all
+// rows of all pairs (red_level: a lane walks kMergeK consecutive rows after a
+// merge-path search, moving on to the next pair in place when it crosses
+// one). ReducePair's row rule (keep t = 0 and value changes) is applied once,
 // to the root, where runs of rows at one time collapse to their first: the
 // same function and the same minimal rows as pruning at every level, since
 // the values at each breakpoint do not depend on which rows the
-// intermediate PCFs kept. The root pass is cut into chunks of rows; the
-// host turns the chunk counts into output offsets.
+// intermediate PCFs kept. The root pass is cut into chunks of rows; red_scan
+// turns the chunk counts into output offsets.
 //
 // Standard deviation. For every breakpoint x of the group's root,
 // (f_i(x) - mean(x))^2 is summed over i in the tree's order (a binary
@@ -192,6 +193,364 @@ __global__ __launch_bounds__(64 * kLevelWaves) void red_level(RedLevelArgs a)
             vout[wb + k] = st_v[wv][k];
         }
         wave_sync_lds();
+    }
+}
+
+
+// ---------------------------------------------------------------------------
+// Several levels of the tree in one pass.
+//
+// A level run alone reads and writes every row and is bound by the chain of
+// dependent loads in front of each window (its pair, the offsets, a search of
+// up to 21 steps): 76 us for 5.5 million FP64 rows at any level. Here a bundle
+// of up to 16 items is merged a tile at a time, four levels in LDS, so a row
+// crosses memory once for four levels: 91 us, and 44 us for the tiles' starts.
+//
+// Tiles. Rows of a bundle are ordered by (time, item, index), the order of
+// the levels' outputs. Every item is sampled each kFuseSpacing rows; a tile
+// starts at every kFuseRanks-th sample of the bundle in that order. Between two
+// neighbouring starts an item has fewer than kFuseSpacing rows beyond those of
+// its samples there, so a tile holds at most kFuseTile rows (24 * 48 on
+// average), whatever the data. That is 31 KiB of LDS in FP64, five workgroups a
+// CU; 16 x 64 (four workgroups) takes 111 us, 32 x 64 119 us, 8 x 64 127 us.
+// red_split finds the samples' ranks, one lane for every (sample, item): a
+// search of the item's samples, summed over the sample's 16 lanes; a sample
+// that starts a tile goes on to its exact row in each item.
+//
+// Values. A row at time x carries h of both sides' values at x (file comment);
+// a side's value at x may come from the row before its part of the tile, or,
+// on equal times, from the row after it. Both are loaded with the tile and
+// merged like the rows: the value before, and the time and value after.
+
+// Entries t[0], t[stride], .. (n of them, in order) below x, or, with `before`,
+// at x too.
+template <typename T>
+__device__ __forceinline__ int64_t fuse_count(const T *t, int64_t n, int64_t stride, T x,
+                                              bool before)
+{
+    int64_t lo = 0, hi = n;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        const T y = t[mid * stride];
+        if (y < x || (before && y == x))
+            lo = mid + 1;
+        else
+            hi = mid;
+    }
+    return lo;
+}
+
+constexpr int kSplitBatch = 2;  // samples of sixteen lanes at once (independent searches)
+
+template <typename T>
+__global__ __launch_bounds__(256) void red_split(RedFuseArgs a)
+{
+    constexpr int N = kSplitBatch;
+    const T *__restrict__ tin = reinterpret_cast<const T *>(a.tin);
+    const int l = threadIdx.x & (kFuseLists - 1);
+    const int shift = (threadIdx.x & 63) & ~(kFuseLists - 1);
+    const int64_t per = (int64_t)blockDim.x / kFuseLists * N;
+    const int64_t span = (int64_t)1 << a.level;
+    // (whole groups of lanes: the lanes past the end repeat the last sample)
+    for (int64_t s0 = blockIdx.x * per; s0 < a.nsamples; s0 += gridDim.x * per) {
+        int64_t bun[N], tile0[N], r[N], n[N], m[N], ui[N], c[N];
+        int own[N];
+        bool live[N];
+        T x[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const int64_t sk = s0 + (int64_t)(threadIdx.x / kFuseLists) * N + k;
+            live[k] = sk < a.nsamples;
+            const int64_t s = live[k] ? sk : a.nsamples - 1;
+            // the bundle of sample s, sixteen candidates a round (the second
+            // sample's is the first's or lies after it)
+            int64_t lo = k == 0 ? 0 : bun[0];
+            int64_t width = k == 0 ? a.nbundles : 1;
+            if (k > 0 && lo + 1 < a.nbundles && a.bundles[lo + 1].sample0 <= s)
+                width = a.nbundles - lo;
+            while (width > 1) {
+                const int64_t step = (width + kFuseLists - 1) / kFuseLists;
+                const bool le = l * step < width && a.bundles[lo + l * step].sample0 <= s;
+                const int got = __popcll((__ballot(le) >> shift) & 0xffffu);  // at least 1
+                lo += (got > 0 ? got - 1 : 0) * step;
+                width -= (got > 0 ? got - 1 : 0) * step;
+                width = width < step ? width : step;
+            }
+            const RedBundle b = a.bundles[lo];
+            bun[k] = lo;
+            tile0[k] = b.tile0;
+            // lane l: item l's rows and samples
+            const int64_t p = b.p0 + l * span < b.pend ? b.p0 + l * span : b.pend;
+            const int64_t pe = p + span < b.pend ? p + span : b.pend;
+            r[k] = a.offsets[p];
+            n[k] = a.offsets[pe] - r[k];
+            m[k] = (n[k] + kFuseSpacing - 1) / kFuseSpacing;
+            int64_t inc = m[k];
+#pragma unroll
+            for (int h = 1; h < kFuseLists; h <<= 1) {
+                const int64_t o = __shfl_up(inc, h, kFuseLists);
+                if (l >= h)
+                    inc += o;
+            }
+            // the sample's item (its samples hold number s - sample0), and
+            // its number there
+            const int64_t u = s - b.sample0;
+            const bool mine = u >= inc - m[k] && u < inc;
+            const uint64_t vote = __ballot(mine) >> shift;
+            own[k] = __builtin_ctz((unsigned)(vote & 0xffffu) | 0x8000u);
+            ui[k] = u - __shfl(inc - m[k], own[k], kFuseLists);
+            x[k] = tin[__shfl(r[k], own[k], kFuseLists) + ui[k] * kFuseSpacing];
+        }
+        // samples of every item below x: the searches in step
+        int64_t lo[N], hi[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            lo[k] = l == own[k] ? ui[k] : 0;
+            hi[k] = l == own[k] ? ui[k] : m[k];
+        }
+        for (;;) {
+            bool more = false;
+            T y[N];
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+                if (lo[k] < hi[k])
+                    y[k] = tin[r[k] + ((lo[k] + hi[k]) >> 1) * kFuseSpacing];
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+                if (lo[k] < hi[k]) {
+                    const int64_t mid = (lo[k] + hi[k]) >> 1;
+                    if (y[k] < x[k] || (l < own[k] && y[k] == x[k]))
+                        lo[k] = mid + 1;
+                    else
+                        hi[k] = mid;
+                    more = more || lo[k] < hi[k];
+                }
+            if (!more)
+                break;
+        }
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            c[k] = lo[k];
+            int64_t rank = c[k];
+#pragma unroll
+            for (int h = 1; h < kFuseLists; h <<= 1)
+                rank += __shfl_xor(rank, h, kFuseLists);
+            if (live[k] && rank % kFuseRanks == 0) {
+                // exact: between the last sample below x and the next one
+                int64_t at = 0;
+                if (l == own[k]) {
+                    at = ui[k] * kFuseSpacing;
+                } else if (c[k] > 0) {
+                    const int64_t base = (c[k] - 1) * kFuseSpacing + 1;
+                    const int64_t end = c[k] * kFuseSpacing < n[k] ? c[k] * kFuseSpacing : n[k];
+                    at = base + fuse_count<T>(tin + r[k] + base, end > base ? end - base : 0, 1,
+                                              x[k], l < own[k]);
+                }
+                int64_t *to = a.split + (tile0[k] + rank / kFuseRanks) * kFuseSplit;
+                to[l] = at;
+                if (l == own[k])
+                    to[kFuseLists] = bun[k];
+            }
+        }
+    }
+}
+
+// (with 512 threads the searches double and the pass takes 146 us; with 128,
+// 149 us: too few waves)
+constexpr int kFuseThreads = 256;
+constexpr int kFuseRun = kFuseTile / kFuseThreads;  // most rows a thread
+
+template <typename T> struct FuseNode {
+    T before, after_v, after_t;  // value before the tile's rows; the row after them
+};
+
+template <typename T, int OP>
+__global__ __launch_bounds__(kFuseThreads) void red_fuse(RedFuseArgs a)
+{
+    const T *__restrict__ tin = reinterpret_cast<const T *>(a.tin);
+    const T *__restrict__ vin = reinterpret_cast<const T *>(a.vin);
+    T *__restrict__ tout = reinterpret_cast<T *>(a.tout);
+    T *__restrict__ vout = reinterpret_cast<T *>(a.vout);
+    __shared__ T lt[kFuseTile], lv[kFuseTile];
+    __shared__ FuseNode<T> node[2][kFuseLists];
+    __shared__ int32_t seg[2][kFuseLists + 1];
+    __shared__ int64_t src[kFuseLists];  // first row of each item's part
+    __shared__ int64_t first_out;
+    const int tid = threadIdx.x;
+    const int64_t span = (int64_t)1 << a.level;
+    const T inf = __builtin_inf();
+    for (int64_t tile = blockIdx.x; tile < a.ntiles; tile += gridDim.x) {
+        // (in bounds also for times that break the order)
+        int64_t lo = a.split[tile * kFuseSplit + kFuseLists];
+        lo = lo < 0 ? 0 : (lo < a.nbundles ? lo : a.nbundles - 1);
+        const RedBundle b = a.bundles[lo];
+        const int64_t tend = lo + 1 < a.nbundles ? a.bundles[lo + 1].tile0 : a.ntiles;
+        const int items = (int)((b.pend - b.p0 + span - 1) / span);
+        if (tid < kFuseLists) {
+            const int64_t p = b.p0 + tid * span < b.pend ? b.p0 + tid * span : b.pend;
+            const int64_t pe = p + span < b.pend ? p + span : b.pend;
+            const int64_t r = a.offsets[p], n = a.offsets[pe] - r;
+            int64_t s = a.split[tile * kFuseSplit + tid];
+            int64_t e = tile + 1 < tend ? a.split[(tile + 1) * kFuseSplit + tid] : n;
+            s = s < 0 ? 0 : (s < n ? s : n);
+            e = e < s ? s : (e < n ? e : n);
+            int64_t skip = s;  // rows of the bundle before the tile
+            int32_t inc = e - s < kFuseTile ? (int32_t)(e - s) : kFuseTile;
+            const int32_t len = inc;
+#pragma unroll
+            for (int h = 1; h < kFuseLists; h <<= 1) {
+                const int32_t o = __shfl_up(inc, h, kFuseLists);
+                if (tid >= h)
+                    inc += o;
+                skip += __shfl_xor(skip, h, kFuseLists);
+            }
+            const int32_t end = inc < kFuseTile ? inc : kFuseTile;
+            const int32_t beg = inc - len < kFuseTile ? inc - len : kFuseTile;
+            e = s + (end - beg);
+            seg[0][tid + 1] = end;
+            if (tid == 0) {
+                seg[0][0] = 0;
+                first_out = a.offsets[b.p0] + skip;
+            }
+            src[tid] = r + s;
+            FuseNode<T> d;
+            d.before = n > 0 ? vin[r + (s > 0 ? s - 1 : 0)] : T(0);
+            d.after_t = e < n ? tin[r + e] : inf;
+            d.after_v = e < n ? vin[r + e] : T(0);
+            node[0][tid] = d;
+        }
+        __syncthreads();
+        const int32_t total = seg[0][kFuseLists];
+        for (int32_t q = tid; q < total; q += kFuseThreads) {
+            int l = 0;  // the item whose part holds row q
+#pragma unroll
+            for (int h = kFuseLists / 2; h > 0; h >>= 1)
+                l += seg[0][l + h] <= q ? h : 0;
+            const int64_t r = src[l] + (q - seg[0][l]);
+            lt[q] = tin[r];
+            lv[q] = vin[r];
+        }
+        __syncthreads();
+        const int32_t run = (total + kFuseThreads - 1) / kFuseThreads;
+        const int32_t q0 = tid * run;
+        const int32_t q1 = q0 + run < total ? q0 + run : total;
+        int cnt = items;
+        for (int lev = 0; lev < a.depth; ++lev) {
+            const int32_t *sg = seg[lev & 1];
+            const FuseNode<T> *nd = node[lev & 1];
+            const int pairs = (cnt + 1) / 2;
+            T xt[kFuseRun], xv[kFuseRun];
+            if (q0 < q1) {
+                int k = 0;  // the pair that holds row q0
+#pragma unroll
+                for (int h = kFuseLists / 4; h > 0; h >>= 1)
+                    k += k + h < pairs && sg[2 * (k + h)] <= q0 ? h : 0;
+                int32_t sA = sg[2 * k], sB = sg[2 * k + 1];
+                int32_t nA = sB - sA, nB = 2 * k + 1 < cnt ? sg[2 * k + 2] - sB : 0;
+                int32_t q = q0 - sA, i, j;
+                {
+                    int32_t l = q - nB > 0 ? q - nB : 0, h = q < nA ? q : nA;
+                    while (l < h) {  // A's share of the first q merged rows
+                        const int32_t mid = (l + h) >> 1;
+                        if (lt[sA + mid] <= lt[sB + (q - 1 - mid)])
+                            l = mid + 1;
+                        else
+                            h = mid;
+                    }
+                    i = l;
+                    j = q - l;
+                }
+// both sides' next rows (or the ones after their parts) and the
+                // values before those
+                T tA, vA, pA, tB, vB, pB;
+                auto heads = [&]() {
+                    const FuseNode<T> &na = nd[2 * k];
+                    tA = i < nA ? lt[sA + i] : na.after_t;
+                    vA = i < nA ? lv[sA + i] : na.after_v;
+                    pA = i > 0 ? lv[sA + i - 1] : na.before;
+                    tB = vB = pB = T(0);
+                    if (2 * k + 1 < cnt) {
+                        const FuseNode<T> &nb = nd[2 * k + 1];
+                        tB = j < nB ? lt[sB + j] : nb.after_t;
+                        vB = j < nB ? lv[sB + j] : nb.after_v;
+                        pB = j > 0 ? lv[sB + j - 1] : nb.before;
+                    }
+                };
+                heads();
+#pragma unroll
+                for (int u = 0; u < kFuseRun; ++u) {
+                    if (q0 + u < q1) {
+                        if (q == nA + nB) {
+                            do {  // the next pair with rows
+                                ++k;
+                                sA = sg[2 * k];
+                                sB = sg[2 * k + 1];
+                                nA = sB - sA;
+                                nB = 2 * k + 1 < cnt ? sg[2 * k + 2] - sB : 0;
+                            } while (nA + nB == 0);
+                            q = i = j = 0;
+                            heads();
+                        }
+                        const bool fromA = i < nA && (j >= nB || tA <= tB);
+                        const T x = fromA ? tA : tB, y = fromA ? vA : vB;
+                        const T ot = fromA ? tB : tA;
+                        const T z = ot == x ? (fromA ? vB : vA) : (fromA ? pB : pA);
+                        xt[u] = x;
+                        // (an unpaired item moves up unchanged)
+                        xv[u] = 2 * k + 1 >= cnt ? y
+                                : fromA          ? red_op<T, OP>(y, z)
+                                                 : red_op<T, OP>(z, y);
+                        ++q;
+                        if (fromA) {
+                            ++i;
+                            pA = y;
+                            tA = i < nA ? lt[sA + i] : nd[2 * k].after_t;
+                            vA = i < nA ? lv[sA + i] : nd[2 * k].after_v;
+                        } else {
+                            ++j;
+                            pB = y;
+                            tB = j < nB ? lt[sB + j] : nd[2 * k + 1].after_t;
+                            vB = j < nB ? lv[sB + j] : nd[2 * k + 1].after_v;
+                        }
+                    }
+                }
+            }
+            // the pairs' parts and the values around them
+            if (tid < pairs) {
+                FuseNode<T> d = nd[2 * tid];
+                int32_t end = sg[2 * tid + 1];
+                if (2 * tid + 1 < cnt) {
+                    const FuseNode<T> A = d, Bn = nd[2 * tid + 1];
+                    const int32_t sA = sg[2 * tid], sB = end;
+                    end = sg[2 * tid + 2];
+                    d.before = red_op<T, OP>(A.before, Bn.before);
+                    d.after_t = A.after_t <= Bn.after_t ? A.after_t : Bn.after_t;
+                    const T va = A.after_t == d.after_t ? A.after_v
+                                                        : (sB > sA ? lv[sB - 1] : A.before);
+                    const T vb = Bn.after_t == d.after_t ? Bn.after_v
+                                                         : (end > sB ? lv[end - 1] : Bn.before);
+                    d.after_v = red_op<T, OP>(va, vb);
+                }
+                node[(lev + 1) & 1][tid] = d;
+                seg[(lev + 1) & 1][tid + 1] = end;
+                if (tid == 0)
+                    seg[(lev + 1) & 1][0] = 0;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kFuseRun; ++u)
+                if (q0 + u < q1) {
+                    lt[q0 + u] = xt[u];
+                    lv[q0 + u] = xv[u];
+                }
+            __syncthreads();
+            cnt = pairs;
+        }
+        for (int32_t q = tid; q < total; q += kFuseThreads) {
+            tout[first_out + q] = lt[q];
+            vout[first_out + q] = lv[q];
+        }
+        __syncthreads();  // (the tile's tables are rewritten next)
     }
 }
 
@@ -596,6 +955,52 @@ __global__ void red_emit(RedEmitArgs a)
     }
 }
 
+// Chunk counts to the chunks' output rows and the groups' offsets (one
+// workgroup; the counts stay on the device, so the host reads the offsets
+// alone and writes nothing back).
+__global__ __launch_bounds__(1024) void red_scan(RedScanArgs a)
+{
+    __shared__ int64_t wsum[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int64_t before = 0;
+    if (tid == 0)
+        a.offsets_out[0] = 0;
+    for (int64_t c0 = 0; c0 < a.nchunks; c0 += 1024) {
+        const int64_t c = c0 + tid;
+        const int64_t n = c < a.nchunks ? a.chunk_cnt[c] : 0;
+        int64_t inc = n;
+#pragma unroll
+        for (int h = 1; h < 64; h <<= 1) {
+            const int64_t o = __shfl_up(inc, h, 64);
+            if (lane >= h)
+                inc += o;
+        }
+        if (lane == 63)
+            wsum[wave] = inc;
+        __syncthreads();
+        int64_t base = before, all = before;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            base += w < wave ? wsum[w] : 0;
+            all += wsum[w];
+        }
+        if (c < a.nchunks) {
+            a.chunk_off[c] = base + inc - n;
+            // a group's last chunk ends its rows
+            if (c + 1 == a.nchunks || a.chunk_grp[c + 1] != a.chunk_grp[c])
+                a.offsets_out[a.chunk_grp[c] + 1] = base + inc;
+        }
+        before = all;
+        __syncthreads();  // (wsum is rewritten next)
+    }
+}
+
+hipError_t launch_red_scan(const RedScanArgs &a, hipStream_t s)
+{
+    hipLaunchKernelGGL(red_scan, dim3(1), dim3(1024), 0, s, a);
+    return hipGetLastError();
+}
+
 static int64_t grid_for(int64_t units, int64_t per_block, int64_t cap)
 {
     int64_t g = (units + per_block - 1) / per_block;
@@ -637,6 +1042,31 @@ hipError_t launch_red_level(bool f64, int op, const RedLevelArgs &a, int64_t row
         launch_red_level_t<double>(op, a, g, blk, s);
     else
         launch_red_level_t<float>(op, a, g, blk, s);
+    return hipGetLastError();
+}
+
+template <typename T>
+static void launch_red_fuse_t(int op, const RedFuseArgs &a, dim3 gs, dim3 gf, hipStream_t s)
+{
+    hipLaunchKernelGGL(red_split<T>, gs, dim3(256), 0, s, a);
+    const dim3 blk(kFuseThreads);
+    switch (op) {
+    case RO_MAX: hipLaunchKernelGGL((red_fuse<T, RO_MAX>), gf, blk, 0, s, a); break;
+    case RO_MIN: hipLaunchKernelGGL((red_fuse<T, RO_MIN>), gf, blk, 0, s, a); break;
+    default: hipLaunchKernelGGL((red_fuse<T, RO_SUM>), gf, blk, 0, s, a); break;  // sum, mean, std
+    }
+}
+
+hipError_t launch_red_fuse(bool f64, int op, const RedFuseArgs &a, hipStream_t s)
+{
+    if (a.ntiles <= 0)
+        return hipSuccess;
+    const dim3 gs((unsigned)grid_for(a.nsamples, 256 / kFuseLists * kSplitBatch, 65536)),
+        gf((unsigned)grid_for(a.ntiles, 1, 65536));
+    if (f64)
+        launch_red_fuse_t<double>(op, a, gs, gf, s);
+    else
+        launch_red_fuse_t<float>(op, a, gs, gf, s);
     return hipGetLastError();
 }
 

@@ -23,6 +23,26 @@ struct RedLevelArgs {
     const void *tin, *vin;
     void *tout, *vout;
 };
+// Several levels in one pass (red_fuse): bundles of at most kFuseLists items.
+constexpr int kFuseLevels = 4;
+constexpr int kFuseLists = 1 << kFuseLevels;
+constexpr int kFuseSpacing = 48;  // rows between a list's samples
+constexpr int kFuseRanks = 24;    // samples between tile starts
+constexpr int kFuseTile = kFuseRanks * kFuseSpacing + kFuseLists * kFuseSpacing;
+constexpr int kFuseSplit = kFuseLists + 1;
+struct RedBundle {
+    int64_t p0, pend;       // its PCFs (one output item)
+    int64_t sample0, tile0; // its first sample and tile
+};
+struct RedFuseArgs {
+    const int64_t *offsets;  // the set's CSR offsets (device, n+1)
+    const RedBundle *bundles;
+    int64_t nbundles, nsamples, ntiles;
+    int level, depth;        // inputs are items of 2^level PCFs, outputs of 2^(level + depth)
+    const void *tin, *vin;
+    void *tout, *vout;
+    int64_t *split;          // scratch, kFuseSplit a tile: where its lists begin, its bundle
+};
 struct RedStdArgs {
     const int64_t *offsets, *groups;
     int32_t B;
@@ -34,6 +54,13 @@ struct RedStdArgs {
     const int64_t *chunk_row, *chunk_grp;
     int64_t *chunk_first;    // scratch, 64 per chunk: PCF i's row at or before
                              // the chunk's first time
+};
+struct RedScanArgs {
+    int64_t nchunks;
+    int32_t B;
+    const int64_t *chunk_cnt, *chunk_grp;
+    int64_t *chunk_off;      // out: the output row of every chunk
+    int64_t *offsets_out;    // out: the B groups' offsets
 };
 struct RedEmitArgs {
     const int64_t *offsets, *groups;
@@ -49,6 +76,8 @@ struct RedEmitArgs {
 };
 hipError_t launch_red_level(bool f64, int op, const RedLevelArgs &a, int64_t rows,
                             hipStream_t s);
+// Levels a.level .. a.level + a.depth - 1 (ops of a tree: sum, max, min).
+hipError_t launch_red_fuse(bool f64, int op, const RedFuseArgs &a, hipStream_t s);
 hipError_t launch_red_interleave(bool f64, int64_t n, const int64_t *xo, const void *xt,
                                  const void *xv, const int64_t *yo, const void *yt,
                                  const void *yv, const int64_t *zo, void *zt, void *zv,
@@ -59,6 +88,7 @@ hipError_t launch_red_std(bool f64, const RedStdArgs &a, hipStream_t s);
 // groups of at most 64 PCFs (a block per chunk of root rows, the PCF rows
 // it selects staged in LDS)
 hipError_t launch_red_std_small(bool f64, const RedStdArgs &a, hipStream_t s);
+hipError_t launch_red_scan(const RedScanArgs &a, hipStream_t s);
 hipError_t launch_red_emit(bool f64, const RedEmitArgs &a, hipStream_t s);
 
 }  // namespace pcf
