@@ -48,6 +48,7 @@ TileShape shape_of(uint32_t flags)
         s.max_block = mb;
     if (bd >= 2 && bd <= 8)
         s.budget_div = bd;
+    s.preset = mb == 0 && bd == 0;
     return s;
 }
 
@@ -370,7 +371,7 @@ pcf_status forward_common(const pcf_set *X, pcf_kind kind, double p, void *out,
         if (st != PCF_OK)
             return st;
         std::string err;
-        // (a workspace sized for the tile plan keeps it)
+        // (a workspace sized for the plan of the largest tiles keeps it)
         for (int cus = device_cus();; cus = 0) {
             if (!plan_matrix(X->n, ho, rec_bytes_of(X->dtype), false, w != nullptr,
                              w ? w->row0 : 0, w ? w->row1 : 0, w ? w->col0 : 0,
@@ -954,7 +955,7 @@ pcf_status pcf_pairwise_batched(int32_t B, const int64_t *set_offsets_host,
         if (st != PCF_OK)
             return st;
         std::string err;
-        // (a workspace sized for the tile plan keeps it)
+        // (a workspace sized for the plan of the largest tiles keeps it)
         for (int cus = device_cus();; cus = 0) {
             if (!plan_batched(B, set_offsets_host, out_offsets_host, ho, all->n,
                               rec_bytes_of(all->dtype),
@@ -1191,7 +1192,7 @@ pcf_status pcf_cross(const pcf_set *X, const pcf_set *Y, pcf_kind kind, double p
     Plan plan;
     const int rb = rec_bytes_of(X->dtype);
     int64_t at = 0, need = 0;
-    // (a workspace sized for the tile plan keeps it)
+    // (a workspace sized for the plan of the largest tiles keeps it)
     for (int cus = device_cus();; cus = 0) {
         st = cross_plan(X, Y, ldo, flags, s, comb, plan, cus);
         if (st != PCF_OK)

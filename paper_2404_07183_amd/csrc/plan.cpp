@@ -349,6 +349,42 @@ bool build_strips(const int64_t *offsets, int64_t lo, int64_t hi,
     return true;
 }
 
+// The most PCFs a block of a tile plan should hold on `cus` CUs. Where the
+// largest blocks give far fewer tiles than CUs, smaller ones spread the steps:
+// a tile then takes its lanes' runs of steps, against a start of workgroups
+// that grows with their number (about 100 steps for one on every CU; beyond
+// two thirds of the CUs nothing is gained). Kernel with its launch, 200 PCFs
+// of 10 to 100 rows, L1 FP64, by PCFs a block: 32 (28 tiles) 31.3 us, 20 25.4,
+// 16 (91 tiles) 23.6, 10 (210 tiles) 23.6, 8 33.2. Not for the adjoint, whose
+// FP32 gradients round once for every tile that adds to them.
+int32_t tile_block_cap(const int64_t *offsets, int64_t lo, int64_t hi,
+                       const std::vector<Region> &regions, int64_t budget, int cus)
+{
+    constexpr double kStartSteps = 100.0, kMostCus = 0.66;
+    const double n = (double)(hi - lo), recs = (double)(offsets[hi] - offsets[lo]) + n * kPad;
+    const double mean = recs / n, steps = 2.0 * (mean - kPad) + kStepBlock / 2;
+    int32_t best = kMaxBlock;
+    double best_time = 0.0;
+    for (int32_t m = kMaxBlock; m >= 4; --m) {
+        const double b = std::min((double)m, std::max(1.0, (double)budget / mean));
+        double tiles = 0.0;
+        for (const Region &g : regions) {
+            const double nr = std::ceil((double)(g.rb - g.ra) / b);
+            tiles += g.map.type == kSegTriangle
+                         ? 0.5 * nr * (nr + 1.0)
+                         : nr * std::ceil((double)(g.cb - g.ca) / b);
+        }
+        if (tiles > kMostCus * cus)
+            break;
+        const double time = b * b * steps / kThreads + kStartSteps * tiles / cus;
+        if (m == kMaxBlock || time < best_time) {
+            best = m;
+            best_time = time;
+        }
+    }
+    return best;
+}
+
 void add_segment(Plan &plan, Segment s, int64_t tiles)
 {
     if (tiles <= 0)
@@ -431,8 +467,12 @@ bool plan_matrix(int64_t n, const int64_t *offsets, int rec_bytes,
         build_strips(offsets, lo, hi, cuts, regions, rec_bytes, shape, cus, plan))
         return true;
 
-    build_blocks(offsets, lo, hi, cuts, block_budget(rec_bytes, backward, shape),
-                 shape.max_block, plan.blocks);
+    const int64_t budget = block_budget(rec_bytes, backward, shape);
+    build_blocks(offsets, lo, hi, cuts, budget,
+                 cus > 0 && !backward && shape.preset
+                     ? tile_block_cap(offsets, lo, hi, regions, budget, cus)
+                     : shape.max_block,
+                 plan.blocks);
     plan.blocks.push_back((int32_t)hi);
     for (const Region &g : regions) {
         Segment s = g.map;
@@ -503,15 +543,18 @@ bool plan_batched(int32_t B, const int64_t *set_offsets,
                      [](const Item &x, const Item &y) { return x.cost > y.cost; });
     if (items.empty())
         return true;
+    int32_t cap = shape.max_block;
+    const int64_t budget = block_budget(rec_bytes, false, shape);
     if (cus > 0) {
         std::vector<Region> regions;
         for (auto &it : items)
             regions.push_back(it.g);
         if (build_strips(offsets, lo, hi, cuts, regions, rec_bytes, shape, cus, plan))
             return true;
+        if (shape.preset)
+            cap = tile_block_cap(offsets, lo, hi, regions, budget, cus);
     }
-    build_blocks(offsets, lo, hi, cuts, block_budget(rec_bytes, false, shape),
-                 shape.max_block, plan.blocks);
+    build_blocks(offsets, lo, hi, cuts, budget, cap, plan.blocks);
     plan.blocks.push_back((int32_t)hi);
     for (auto &it : items) {
         Segment s = it.g.map;

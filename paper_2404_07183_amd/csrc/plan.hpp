@@ -44,6 +44,7 @@ struct Plan {
 struct TileShape {
     int32_t max_block = kMaxBlock;
     int32_t budget_div = 2;
+    bool preset = true;  // neither was asked for
 };
 
 // Records a block may hold.
@@ -60,7 +61,8 @@ void build_blocks(const int64_t *offsets, int64_t lo, int64_t hi,
 // Plan for one n x n matrix, or the window [r0,r1) x [c0,c1) of it.
 // Returns false with a message in `err` on bad input. With cus > 0 (the
 // device's CUs) a forward plan is a strip plan where that pays (build_strips),
-// else, and always with 0, a tile plan.
+// and the blocks of a small tile plan are sized for the device
+// (tile_block_cap); with 0 it is the tile plan of the largest blocks.
 bool plan_matrix(int64_t n, const int64_t *offsets, int rec_bytes,
                  bool backward, bool windowed, int64_t r0, int64_t r1,
                  int64_t c0, int64_t c1, bool upper_only, int64_t ldo,

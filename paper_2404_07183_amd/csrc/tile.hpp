@@ -386,9 +386,10 @@ __device__ __forceinline__ void pair_start(Src src, int32_t A, int32_t na,
 // at most kThreads - 64 pairs.
 constexpr int kQueueLane = kThreads - 64;
 
-// Takes the next ticket from the tile queue. The ticket stays 32-bit until
-// it is decoded, so that no instruction reads the returned value (and waits
-// for it) before the decode, after the merge work.
+// Takes the next ticket from the tile queue (its value plus the workgroups'
+// own first tiles is the tile, see TileLoop::start). The ticket stays 32-bit
+// until it is decoded, so that no instruction reads the returned value (and
+// waits for it) before the decode, after the merge work.
 __device__ __forceinline__ uint32_t tile_ticket(const unsigned char *ws)
 {
     uint32_t *counter =
@@ -889,16 +890,20 @@ struct TileLoop {
     __device__ __forceinline__ int nxt() const { return cur == 2 ? 0 : cur + 1; }
     __device__ __forceinline__ int aft() const { return cur == 0 ? 2 : cur - 1; }
 
-    // decode the first two tiles, stage the first one
+    // decode the first two tiles, stage the first one. A workgroup's first
+    // tile is its own number, so two lanes of different waves decode both at
+    // once and only the second waits for a ticket: a launch of one round of
+    // tiles is mostly this chain of dependent loads (200 PCFs in 28 tiles, L1
+    // FP64: 35 -> 31 us; 500 PCFs of 20 to 300 rows: 67 -> 41 us).
     template <typename T, bool Direct, typename Sh>
     __device__ __forceinline__ void start(Sh &sh, const unsigned char *ws,
                                           const int64_t *offsets, Rec<T> *lrec,
                                           const Rec<T> *grec)
     {
-        if (threadIdx.x == kQueueLane) {
-            tile_decode(sh.desc[0], tile_ticket(ws), ws, offsets);
-            tile_decode(sh.desc[1], tile_ticket(ws), ws, offsets);
-        }
+        if (threadIdx.x == 0)
+            tile_decode(sh.desc[0], blockIdx.x, ws, offsets);
+        else if (threadIdx.x == kQueueLane)
+            tile_decode(sh.desc[1], (int64_t)gridDim.x + tile_ticket(ws), ws, offsets);
         sync_lds();
         if (sh.desc[0].tile < hdr_of(ws).ntiles) {
             StageRegs<T, Direct> g;
@@ -926,7 +931,7 @@ struct TileLoop {
                                                 const int64_t *offsets)
     {
         if (threadIdx.x == kQueueLane)
-            tile_decode(sh.desc[aft()], ticket, ws, offsets);
+            tile_decode(sh.desc[aft()], (int64_t)gridDim.x + ticket, ws, offsets);
     }
     // whether there is a next tile (its descriptor, decoded one tile ago)
     template <typename Sh>

@@ -132,6 +132,28 @@ int main()
     }
     for (int x : seen)
         CHECK(x == 1);
+    // small tile plans: smaller blocks on a device of 256 CUs, none where a
+    // shape is asked for or the plan is an adjoint's
+    for (int64_t n : {2, 31, 33, 200, 450, 3000}) {
+        std::vector<int64_t> of(1, 0);
+        for (int64_t i = 0; i < n; ++i)
+            of.push_back(of.back() + U(10, 100));
+        Plan big, cap, shaped, adj0, adj;
+        TileShape sh;
+        sh.preset = false;
+        CHECK(plan_matrix(n, of.data(), 16, false, false, 0, 0, 0, 0, false, n, TileShape(), big, e));
+        CHECK(plan_matrix(n, of.data(), 16, false, false, 0, 0, 0, 0, false, n, TileShape(), cap, e, 256));
+        CHECK(plan_matrix(n, of.data(), 16, false, false, 0, 0, 0, 0, false, n, sh, shaped, e, 256));
+        CHECK(plan_matrix(n, of.data(), 16, true, false, 0, 0, 0, 0, false, n, TileShape(), adj0, e));
+        CHECK(plan_matrix(n, of.data(), 16, true, false, 0, 0, 0, 0, false, n, TileShape(), adj, e, 256));
+        CHECK(adj.blocks == adj0.blocks && (shaped.strips || shaped.blocks == big.blocks));
+        if (cap.strips)
+            continue;
+        const int64_t nb = (int64_t)cap.blocks.size() - 1;
+        CHECK(cap.ntiles == nb * (nb + 1) / 2 && cap.blocks.front() == 0 && cap.blocks.back() == n);
+        CHECK(cap.blocks == big.blocks || cap.ntiles <= 169);
+        CHECK(n != 200 || cap.blocks.size() > big.blocks.size());
+    }
     std::printf("ok %d strip plans, %d tile plans\n", strips, tiles);
 }
 """
