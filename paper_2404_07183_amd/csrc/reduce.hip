@@ -34,6 +34,8 @@
 // and x -> sqrt(x / (n - 1)) are applied.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "launch.hpp"
 #include "reduce.hpp"
 
@@ -671,19 +673,31 @@ __global__ void red_std_terms(RedStdArgs a)
 // (c1 - c0) + 2m - 1 rows over the group (one per root row c0 + 1 .. c1,
 // m - 1 more that tie with x1 past it, and the m rows at or before xf).
 // red_std_bounds bisects every PCF once per chunk for the rows at or before
-// xf; red_std_small stages the window of (t, v) records in LDS. Thread j
-// then takes root rows c0 + Rj .. c0 + Rj + R - 1: for every PCF i of the
-// group (i = 0, 1, .. in order) it finds the record at or before its first
-// row by bisection of PCF i's records, walks forward for the others, and adds
-// (f_i(x) - mean(x))^2 to a binary counter per row, which sums the m terms in
-// the reduction tree's order (pairs (2j, 2j + 1), then pairs of pairs, an
-// unpaired last block moving up), as red_std_terms.
+// xf; red_std_small stages the window of (t, v) records in LDS.
+//
+// A record of the window that lies past xf is one root row of the chunk: it
+// is found there by one bisection of the chunk's times, and its PCF noted as
+// the row's owner (any order within a run of equal times will do, since every
+// row of the run selects by the run's last). The record that PCF i gives a row
+// is then a count: its records before the row's block of 64, and, by a ballot
+// over the block's owners, those up to the row. One bisection a record in place
+// of one for every PCF and two rows: 1,000 groups of 20 PCFs, 5.5 million FP64
+// rows, 111 us against 166 (bound by the chain of dependent reads of a chunk:
+// at 64 VGPRs, and so four blocks a CU, 111 us, at 78 VGPRs and three 133). A
+// block whose last row ties with the next one bisects every PCF for each of its
+// rows instead. Each lane takes one row and adds
+// (f_i(x) - mean(x))^2 to a binary counter, which sums the m terms in the
+// reduction tree's order (pairs (2j, 2j + 1), then pairs of pairs, an unpaired
+// last block moving up), as red_std_terms.
 constexpr int kStdThreads = 512;
-constexpr int kStdRowsPerThread = kChunkRows / kStdThreads;
+constexpr int kStdBlocks = kChunkRows / 64;
+constexpr int kStdRows = kChunkRows / kStdThreads;
 constexpr int kStdWindow = kChunkRows + 2 * (int)kStdSmall;
-constexpr int kStdHeights = 7;  // subtree heights 0 .. 6: up to 127 >= kStdSmall terms
-constexpr int kStdBatch = 4;  // PCFs whose bisections run together
-static_assert(kChunkRows % kStdThreads == 0 && kStdSmall == 64 && (1 << kStdHeights) > kStdSmall,
+constexpr int kStdLoads = (kStdWindow + kStdThreads - 1) / kStdThreads;
+constexpr int kStdBatch = 4;  // PCFs whose values are read together
+constexpr int kStdHeights = 5;  // subtrees of kStdBatch 2^h terms
+static_assert(kChunkRows % kStdThreads == 0 && kStdSmall == 64 &&
+                  (kStdBatch << kStdHeights) > kStdSmall,
               "red_std_small's layout");
 
 // chunk_first[64c + i] = the last row of PCF i (i < m) with t at or before
@@ -720,35 +734,42 @@ struct StdRecord {
     T t, v;
 };
 
-// Term s[k] joins the subtrees of heights 0 .. H-1 (smallest first, each on
-// the left) and is kept as the subtree of height H.
-template <typename T, int R, int H>
-__device__ __forceinline__ void std_counter_add(T (&st)[R][kStdHeights], T (&s)[R])
+// Subtree number j (from 0) of kStdBatch terms in the binary counter: after
+// j + 1 of them st[h] holds a complete subtree of kStdBatch 2^h terms for every
+// set bit h of j + 1; s joins the subtrees below the lowest clear bit of j,
+// smallest first, each on the left. (Fixed indices: a loop over h becomes one
+// store at a variable index, and that a copy of all of st for every subtree.)
+template <int h, typename T>
+__device__ __forceinline__ void std_join(T (&st)[kStdHeights], T s, int j)
 {
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-#pragma unroll
-        for (int h = 0; h < H; ++h)
-            s[k] = st[k][h] + s[k];
-        st[k][H] = s[k];
+#pragma clang fp contract(off)
+    if constexpr (h == kStdHeights - 1) {
+        st[h] = s;
+    } else {
+        if ((j >> h) & 1)  // (j is the same on every lane)
+            std_join<h + 1>(st, st[h] + s, j);
+        else
+            st[h] = s;
     }
 }
 
 template <typename T>
-__global__ __launch_bounds__(kStdThreads) void red_std_small(RedStdArgs a)
+__global__ __launch_bounds__(kStdThreads, 8) void red_std_small(RedStdArgs a)
 {
 #pragma clang fp contract(off)
-    constexpr int R = kStdRowsPerThread;
     const T *__restrict__ t = reinterpret_cast<const T *>(a.t);
     const T *__restrict__ v = reinterpret_cast<const T *>(a.v);
     const T *__restrict__ rt = reinterpret_cast<const T *>(a.rt);
     const T *__restrict__ rv = reinterpret_cast<const T *>(a.rv);
     T *__restrict__ q = reinterpret_cast<T *>(a.q);
     __shared__ StdRecord<T> rec[kStdWindow];
+    __shared__ T times[kChunkRows + 1];  // inf past the group's rows
+    __shared__ int32_t owner[kChunkRows];  // the row's PCF, -1: none
+    __shared__ int32_t first[kStdBlocks][kStdSmall];  // counts, then the first record
     __shared__ int64_t row0[kStdSmall];
     __shared__ int32_t wbase[kStdSmall + 1];
     __shared__ int32_t bad;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
     const T inf = __builtin_inf();
     for (int64_t c = blockIdx.x; c < a.nchunks; c += gridDim.x) {
         const int64_t b = a.chunk_grp[c];
@@ -758,6 +779,7 @@ __global__ __launch_bounds__(kStdThreads) void red_std_small(RedStdArgs a)
             continue;  // red_std_terms' rows (block-uniform)
         const int64_t c0 = a.chunk_row[c], g1 = a.offsets[gb + m];
         const int64_t c1 = c0 + kChunkRows < g1 ? c0 + kChunkRows : g1;
+        const int rows = (int)(c1 - c0);
         // window offsets: an inclusive scan of the record counts in wave 0
         if (tid < 64) {
             int64_t len = 0;
@@ -784,125 +806,158 @@ __global__ __launch_bounds__(kStdThreads) void red_std_small(RedStdArgs a)
                 bad = over != 0;
             }
         }
+        T mean[kStdRows];  // of the thread's rows tid + u kStdThreads
+#pragma unroll
+        for (int u = 0; u < kStdRows; ++u) {
+            const int r = tid + u * kStdThreads;
+            times[r] = r < rows ? rt[c0 + r] : inf;
+            mean[u] = r < rows ? rv[c0 + r] : T(0);
+            owner[r] = -1;
+        }
+        if (tid == 0)
+            times[kChunkRows] = c1 < g1 ? rt[c1] : inf;
+        for (int r = tid; r < kStdBlocks * (int)kStdSmall; r += kStdThreads)
+            (&first[0][0])[r] = 0;
         __syncthreads();
         const int32_t L = wbase[m];
         const bool ok = bad == 0;
+        int32_t pcf[kStdLoads];
         if (ok) {
-            for (int32_t e = tid; e < L; e += kStdThreads) {
-                int32_t lo = 0, hi = m - 1;  // the PCF whose window holds record e
-                while (lo < hi) {
-                    const int32_t mid = (lo + hi + 1) >> 1;
-                    if (wbase[mid] <= e)
-                        lo = mid;
-                    else
-                        hi = mid - 1;
-                }
-                const int64_t r = row0[lo] + (e - wbase[lo]);
-                rec[e].t = t[r];
-                rec[e].v = v[r];
-            }
-        }
-        // this thread's root rows and their means (rows past the chunk repeat
-        // its last time and are not written)
-        const int64_t r0 = c0 + (int64_t)R * tid;
-        T x[R], mean[R];
 #pragma unroll
-        for (int k = 0; k < R; ++k) {
-            const int64_t r = r0 + k < c1 ? r0 + k : c1 - 1;
-            x[k] = rt[r];
-            mean[k] = rv[r] / (T)m;
+            for (int u = 0; u < kStdLoads; ++u) {
+                const int32_t e = tid + u * kStdThreads;
+                int32_t lo = 0;  // the PCF whose window holds record e
+#pragma unroll
+                for (int32_t h = (int32_t)kStdSmall / 2; h > 0; h >>= 1)
+                    lo += lo + h < m && wbase[lo + h] <= e ? h : 0;
+                pcf[u] = lo;
+                if (e < L) {
+                    const int64_t r = row0[lo] + (e - wbase[lo]);
+                    rec[e].t = t[r];
+                    rec[e].v = v[r];
+                }
+            }
+            // the records' rows (the first of a PCF's window lies at or
+            // before the chunk's first time, some of the last past its end)
+            const auto place = [&](auto from, auto to) {
+                int32_t at[kStdLoads];  // rows with times below x
+                T x[kStdLoads];
+#pragma unroll
+                for (int u = from; u < to; ++u) {
+                    const int32_t e = tid + u * kStdThreads;
+                    x[u] = rec[e < kStdWindow ? e : 0].t;
+                    at[u] = 0;
+                }
+#pragma unroll
+                for (int32_t h = kChunkRows / 2; h > 0; h >>= 1)
+#pragma unroll
+                    for (int u = from; u < to; ++u)
+                        at[u] += times[at[u] + h - 1] < x[u] ? h : 0;
+#pragma unroll
+                for (int u = from; u < to; ++u) {
+                    const int32_t e = tid + u * kStdThreads;
+                    if (e < L && e > wbase[pcf[u]]) {
+                        for (int32_t k = at[u]; k < rows && times[k] == x[u]; ++k)
+                            if (atomicCAS(&owner[k], -1, pcf[u]) == -1) {
+                                atomicAdd(&first[k >> 6][pcf[u]], 1);
+                                break;
+                            }
+                    }
+                }
+            };
+            using std::integral_constant;
+            place(integral_constant<int, 0>(), integral_constant<int, kStdRows>());
+            if (kStdRows * kStdThreads + __builtin_amdgcn_readfirstlane(tid) < L)
+                place(integral_constant<int, kStdRows>(), integral_constant<int, kStdLoads>());
         }
         __syncthreads();
-        T st[R][kStdHeights];
+        if (tid < m) {
+            int32_t at = wbase[tid];
 #pragma unroll
-        for (int k = 0; k < R; ++k)
-#pragma unroll
-            for (int h = 0; h < kStdHeights; ++h)
-                st[k][h] = T(0);
-        if (ok) {
-            // kStdBatch PCFs at a time: their bisections are independent
-            // chains of LDS reads, interleaved; their terms then join the
-            // counter in PCF order, as one PCF at a time would
-            for (int i0 = 0; i0 < m; i0 += kStdBatch) {
-                int32_t lo[kStdBatch], end[kStdBatch], p[kStdBatch];
-                int32_t span = 1;
-#pragma unroll
-                for (int u = 0; u < kStdBatch; ++u) {
-                    // (past the group: the last PCF again, its terms unused)
-                    const int i = i0 + u < m ? i0 + u : m - 1;
-                    lo[u] = __builtin_amdgcn_readfirstlane(wbase[i]);
-                    end[u] = __builtin_amdgcn_readfirstlane(wbase[i + 1]);
-                    p[u] = lo[u];
-                    span = end[u] - lo[u] > span ? end[u] - lo[u] : span;
-                }
-                // last record of each PCF at or before x[0] (rec[lo].t <=
-                // x[0]); steps of one power of two for all, whose sum
-                // covers the widest window
-                int32_t step = 1;
-                while (2 * step <= span - 1)
-                    step <<= 1;
-                for (int32_t s = span > 1 ? step : 0; s > 0; s >>= 1) {
-#pragma unroll
-                    for (int u = 0; u < kStdBatch; ++u) {
-                        const int32_t j = p[u] + s;
-                        if (j < end[u] && rec[j].t <= x[0])
-                            p[u] = j;
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < kStdBatch; ++u) {
-                    if (i0 + u >= m)
-                        break;
-                    int32_t pr = p[u];
-                    T val[R];
-                    val[0] = rec[pr].v;
-                    T nt = pr + 1 < end[u] ? rec[pr + 1].t : inf;
-#pragma unroll
-                    for (int k = 1; k < R; ++k) {
-                        while (nt <= x[k]) {
-                            ++pr;
-                            nt = pr + 1 < end[u] ? rec[pr + 1].t : inf;
-                        }
-                        val[k] = rec[pr].v;
-                    }
-                    T s[R];
-#pragma unroll
-                    for (int k = 0; k < R; ++k) {
-                        const T d = val[k] - mean[k];
-                        s[k] = d * d;
-                    }
-                    // binary counter: after i + 1 terms st[k][h] holds a
-                    // complete subtree of 2^h terms for every set bit h of
-                    // i + 1; term i joins the subtrees below the lowest
-                    // clear bit of i
-                    switch (__builtin_ctz(~(unsigned)(i0 + u))) {
-                    case 0: std_counter_add<T, R, 0>(st, s); break;
-                    case 1: std_counter_add<T, R, 1>(st, s); break;
-                    case 2: std_counter_add<T, R, 2>(st, s); break;
-                    case 3: std_counter_add<T, R, 3>(st, s); break;
-                    case 4: std_counter_add<T, R, 4>(st, s); break;
-                    case 5: std_counter_add<T, R, 5>(st, s); break;
-                    default: std_counter_add<T, R, 6>(st, s); break;
-                    }
-                }
+            for (int k = 0; k < kStdBlocks; ++k) {
+                const int32_t n = first[k][tid];
+                first[k][tid] = at;
+                at += n;
             }
         }
-        // fold the subtrees from the smallest up and store
+        __syncthreads();
 #pragma unroll
-        for (int k = 0; k < R; ++k) {
-            T acc = T(0);
-            bool have = false;
+        for (int w = 0; w < kStdRows; ++w) {
+            const int blk = __builtin_amdgcn_readfirstlane(tid >> 6) + w * (kStdThreads / 64);
+            if (blk * 64 >= rows)
+                break;
+            const int r = blk * 64 + lane;
+            const bool live = r < rows;
+            const T x = times[r];
+            const T mu = mean[w] / (T)m;
+            const int32_t own = owner[r];
+            const uint64_t same = __ballot(live && times[r + 1] == x);
+            const int last = rows - blk * 64 < 64 ? rows - blk * 64 - 1 : 63;
+            const bool tied = (same >> last) & 1;
+            // rows up to the end of this row's run of equal times
+            const int end = lane + __builtin_ctzll(~(same >> lane));
+            const uint64_t upto = end >= 63 ? ~0ull : (2ull << end) - 1;
+            const uint32_t ulo = (uint32_t)upto, uhi = (uint32_t)(upto >> 32);
+            T st[kStdHeights], acc = T(0);
+#pragma unroll
+            for (int h = 0; h < kStdHeights; ++h)
+                st[h] = T(0);
+            bool have = false;  // acc holds the group's last m % kStdBatch terms
+            for (int i0 = 0; ok && i0 < m; i0 += kStdBatch) {
+                T d[kStdBatch];
+                if (tied) {
+#pragma unroll 1
+                    for (int u = 0; u < kStdBatch; ++u) {
+                        const int i = i0 + u < m ? i0 + u : m - 1;
+                        int32_t lo = wbase[i], hi = wbase[i + 1] - 1;
+                        while (lo < hi) {  // rec[lo].t <= x
+                            const int32_t mid = (lo + hi + 1) >> 1;
+                            if (rec[mid].t <= x)
+                                lo = mid;
+                            else
+                                hi = mid - 1;
+                        }
+                        const T f = rec[lo].v;
+#pragma unroll
+                        for (int j = 0; j < kStdBatch; ++j)
+                            d[j] = j == u ? f : d[j];
+                    }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < kStdBatch; ++u) {
+                        // (past the group: the last PCF again, not used)
+                        const int i = i0 + u < m ? i0 + u : m - 1;
+                        const uint64_t mine = __builtin_amdgcn_ballot_w64(own == i);
+                        d[u] = rec[first[blk][i] + __popc((uint32_t)mine & ulo) +
+                                   __popc((uint32_t)(mine >> 32) & uhi)].v;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kStdBatch; ++u) {
+                    d[u] -= mu;
+                    d[u] *= d[u];
+                }
+                const T pair = d[0] + d[1];
+                const int left = m - i0;
+                if (left >= kStdBatch) {
+                    std_join<0>(st, pair + (d[2] + d[3]), i0 / kStdBatch);
+                } else {
+                    have = true;
+                    acc = left == 1 ? d[0] : left == 2 ? pair : pair + d[2];
+                }
+            }
+            // fold the subtrees from the smallest up and store
 #pragma unroll
             for (int h = 0; h < kStdHeights; ++h) {
-                if ((m >> h) & 1) {
-                    acc = have ? st[k][h] + acc : st[k][h];
+                if ((m / kStdBatch >> h) & 1) {
+                    acc = have ? st[h] + acc : st[h];
                     have = true;
                 }
             }
-            if (r0 + k < c1)
-                q[r0 + k] = ok ? acc : __builtin_nan("");
+            if (live)
+                q[c0 + r] = ok ? acc : __builtin_nan("");
         }
-        __syncthreads();  // the records and window table are rewritten next
+        __syncthreads();  // the records and tables are rewritten next
     }
 }
 
