@@ -130,10 +130,17 @@ constexpr double strip_ring(int rec_bytes, int64_t mean)
 // `spread` is the mean square of the row counts over their squared mean:
 // columns of very different lengths make waves wait for the oldest one's place
 // in the ring (128 problems of geometric row counts, spread 2: 2350 / 2500).
-bool strips_pay(double mean, double spread, double K, int rec_bytes)
+// A strip plan also takes the host longer to make and to copy, by about 25 us
+// and 5 us more for every thousand PCFs. With short PCFs, whose gain goes with
+// the pairs a lane, that decides for sets used once (L1 FP64, rows 46, tile
+// kernel / strip kernel, us, set used again and new): 1,600 PCFs 126 / 125 and
+// 133 / 157; 2,200 229 / 182 and 237 / 221; 3,000 381 / 294 and 390 / 331; a
+// window of 600 rows and 4,400 columns 195 / 188 and 209 / 244.
+bool strips_pay(double mean, double spread, double K, double lane_pairs, int64_t pcfs,
+                int rec_bytes)
 {
     if (mean <= 64.0)
-        return K >= 200.0;
+        return K >= 200.0 && lane_pairs >= 3.0 + (double)pcfs / 600.0;
     if (spread > 1.6)
         return false;
     if (rec_bytes == 16)
@@ -166,8 +173,9 @@ bool build_strips(const int64_t *offsets, int64_t lo, int64_t hi,
     // s = sqrt(2 K kItemSteps).
     const double mean_steps = 2.0 * (double)(mean - kPad);
     const double rows = (double)(offsets[hi] - offsets[lo]) / (double)(hi - lo);
-    if (!strips_pay(rows, squares / (double)(hi - lo) / (rows * rows),
-                    pairs * mean_steps / (64.0 * cus * kStripWaves), rec_bytes))
+    const double lane_pairs = pairs / (64.0 * cus * kStripWaves);
+    if (!strips_pay(rows, squares / (double)(hi - lo) / (rows * rows), lane_pairs * mean_steps,
+                    lane_pairs, hi - lo, rec_bytes))
         return false;
     int waves = kStripWaves;
     int64_t R = 0, M = 1, ring = 0, area = 0;
@@ -212,7 +220,12 @@ bool build_strips(const int64_t *offsets, int64_t lo, int64_t hi,
     // column groups: at most M PCFs, within one block, at their ring places
     const int64_t most_recs = std::max(longest, M * mean * 5 / 4);
     std::vector<int32_t> gfirst((size_t)nblk + 1);
+    std::vector<double> gcost;  // rows of the groups before each
+    const size_t most_groups = (size_t)(M == 1 ? hi - lo : (hi - lo) * 2 / M + nblk) + 1;
     plan.groups.clear();
+    plan.groups.reserve(most_groups);
+    gcost.reserve(most_groups);
+    plan.sblocks.reserve((size_t)nblk);
     uint32_t virt = 0;
     int64_t at = 0;  // virt modulo the ring
     auto place = [&](int64_t start, int64_t cols, int64_t len) {
@@ -222,6 +235,7 @@ bool build_strips(const int64_t *offsets, int64_t lo, int64_t hi,
         }
         plan.groups.push_back({(int32_t)start, (int32_t)(offsets[start] + start * kPad),
                                (int32_t)(len + (cols << kStripColShift)), virt});
+        gcost.push_back((double)(offsets[start] - offsets[lo]));
         virt += (uint32_t)len;
         at += len;
     };
@@ -244,6 +258,7 @@ bool build_strips(const int64_t *offsets, int64_t lo, int64_t hi,
     }
     gfirst[(size_t)nblk] = (int32_t)plan.groups.size();
     plan.groups.push_back({(int32_t)hi, 0, 0, virt});
+    gcost.push_back((double)(offsets[hi] - offsets[lo]));
 
     plan.strips = true;
     plan.strip_waves = waves;
@@ -256,17 +271,12 @@ bool build_strips(const int64_t *offsets, int64_t lo, int64_t hi,
     // CU unless the launch is long (then the queue evens out what the cost
     // misses); a run that crosses row blocks holds several jobs.
     // (a block's cost over groups [g0, g1) by prefix sums of group records)
-    std::vector<double> gcost(plan.groups.size());
     auto range_cost = [&](int64_t rows, int64_t rowrows, int64_t g0, int64_t g1) {
         const double m = (double)(plan.groups[(size_t)g1].start - plan.groups[(size_t)g0].start);
         return (double)(g1 - g0) * kItemSteps +
                ((double)rows * (gcost[(size_t)g1] - gcost[(size_t)g0]) + m * (double)rowrows) /
                    64.0;
     };
-    gcost[0] = 0.0;
-    for (size_t g = 0; g + 1 < plan.groups.size(); ++g)
-        gcost[g + 1] = gcost[g] + (double)(offsets[plan.groups[g + 1].start] -
-                                           offsets[plan.groups[g].start]);
     double total = 0.0, items = 0.0;
     for (Region &g : regions) {
         if (g.map.type == kSegRect && g.rb - g.ra > g.cb - g.ca) {
@@ -317,12 +327,41 @@ bool build_strips(const int64_t *offsets, int64_t lo, int64_t hi,
                 // the groups that fit the run (records of a job's columns stay
                 // below 2^28, see busy in strips.hip)
                 const double room = target - used - kJobSteps * waves;
+                auto fits = [&](int64_t g) {
+                    return range_cost(rows, rowrows, g0, g) <= room &&
+                           plan.groups[(size_t)g].virt - plan.groups[(size_t)g0].virt <
+                               (1u << 28);
+                };
+                // most groups within the room (at least one): from where the
+                // row block's mean cost a group puts it, by growing steps
+                const double guess =
+                    room * (double)(gend - g0) / range_cost(rows, rowrows, g0, gend);
                 int64_t lo_ = g0 + 1, hi_ = gend;
-                while (lo_ < hi_) {  // most groups within the room
+                if (guess < (double)(gend - g0)) {
+                    const int64_t g = std::max(lo_, g0 + (int64_t)guess);
+                    if (g == lo_ || fits(g)) {
+                        lo_ = g;
+                        for (int64_t d = 1; lo_ + d <= gend; d *= 2) {
+                            if (!fits(lo_ + d)) {
+                                hi_ = lo_ + d - 1;
+                                break;
+                            }
+                            lo_ += d;
+                        }
+                    } else {
+                        hi_ = g - 1;
+                        for (int64_t d = 1; hi_ - d > lo_; d *= 2) {
+                            if (fits(hi_ - d)) {
+                                lo_ = hi_ - d;
+                                break;
+                            }
+                            hi_ -= d;
+                        }
+                    }
+                }
+                while (lo_ < hi_) {
                     const int64_t mid = (lo_ + hi_ + 1) / 2;
-                    if (range_cost(rows, rowrows, g0, mid) <= room &&
-                        plan.groups[(size_t)mid].virt - plan.groups[(size_t)g0].virt <
-                            (1u << 28))
+                    if (fits(mid))
                         lo_ = mid;
                     else
                         hi_ = mid - 1;
