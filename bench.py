@@ -11,7 +11,7 @@ with inputs resident in HBM. Prints ONE JSON line.
 The JSON carries the whole-call throughput (pair integrals per second over
 the N(N-1)/2 upper-triangle pairs), the dominant kernel's roofline entry
 (FP64 VALU lane-operations; its duration from HIP events around calls that
-only launch the tile kernel) and the CPU oracle timed on a bounded sample on
+only launch the pair kernel) and the CPU oracle timed on a bounded sample on
 this host's cores. Unless --no-extras, it also carries the extra lines:
 batched (512 independent matrices), fwd_bwd (forward + adjoint), cross
 (10,000 x 20,000 cross-set matrix), single (L2 norms) and reduce (mean and
@@ -45,13 +45,13 @@ OPS_PER_STEP = {"l1": 4, "l2sq": 5, "l2": 5, "gram": 4}  # algorithmic FP64 ops
 ADJ_OPS = {"l2sq": 12, "gram": 8}
 
 
-# the sources the tile kernel, its launch arguments and its plan are built from
+# the sources the pair kernels, their launch arguments and their plans are built from
 TILE_SOURCES = ("common.hpp", "kernels.hip", "launch.hpp", "plan.cpp", "plan.hpp", "strips.hip",
                 "tile.hpp")
 
 
 def kernel_source_digest():
-    """SHA-256 over the tile kernel's sources (file names and contents, in
+    """SHA-256 over the pair kernels' sources (file names and contents, in
     TILE_SOURCES order): identifies the kernel build that counters were
     taken on."""
     import hashlib
@@ -64,8 +64,13 @@ def kernel_source_digest():
     return h.hexdigest()
 
 
+def strip_plan(ws):
+    """Whether a workspace holds a strip plan (strip_pairs of its header)."""
+    return int.from_bytes(ws.buf[192:196].cpu().numpy().tobytes(), "little") > 0
+
+
 def measured_traffic(key):
-    """HBM bytes per launch of the tile kernel for workload `key`, from the
+    """HBM bytes per launch of the pair kernel for workload `key`, from the
     committed counter summary (FETCH_SIZE and WRITE_SIZE, each scaled by the
     same counter's reading for a copy of known size); None when there is no
     entry or the sources changed since the counters were taken."""
@@ -173,7 +178,7 @@ def run_plain(args):
     wall = time.perf_counter() - t_wall
     ms_step = e0.elapsed_time(e1) / args.steps
     # dominant kernel alone: same calls with the records already packed, so
-    # each call launches only the counter reset and the tile kernel
+    # each call launches only the counter reset and the pair kernel
     k0 = torch.cuda.Event(enable_timing=True)
     k1 = torch.cuda.Event(enable_timing=True)
     k0.record(stream)
@@ -214,8 +219,8 @@ def run_plain(args):
             "unit": "TOP/s",
             "frac": achieved / PEAK_FP64_LANE_OPS,
             "traffic": measured_traffic("plain-%s-%s-n%d" % (args.kind, args.dtype, N)),
-            "kernel": "pairwise_tiles<%s,%s>" % ("double" if args.dtype == "f64" else "float",
-                                                  args.kind),
+            "kernel": "%s<%s,%s>" % ("pairwise_strips" if strip_plan(ws) else "pairwise_tiles",
+                                     "double" if args.dtype == "f64" else "float", args.kind),
             "kernel_ms": ms_kernel,
             "ops_per_step": OPS_PER_STEP[args.kind],
         },
@@ -427,9 +432,9 @@ def run_single(steps, warmup):
 
 def run_reduce(steps, warmup):
     """Mean of the plain 20,000-PCF set (FP64) as one group: a binary tree of
-    15 levels, each reading and writing about every row once (continuous
-    times share no breakpoints), then the root's rows. Algorithmic bytes:
-    per level, t and v of every input row read and of every output row
+    15 levels in passes of four, each reading and writing about every row once
+    (continuous times share no breakpoints), then the root's rows. Algorithmic
+    bytes: per pass, t and v of every input row read and of every output row
     written; the root read twice (count, fill) and written once. The time is
     the whole api.reduce call, host round trip for the output size included.
     Also the std of 1,000 groups of 20 PCFs."""
@@ -453,7 +458,7 @@ def run_reduce(steps, warmup):
     P = int(o[-1])
     levels = int(np.ceil(np.log2(X.n)))
     root = res["mean_one_group"]["out_rows"]
-    nbytes = levels * 2 * P * 16 + 3 * root * 16
+    nbytes = -(-levels // 4) * 2 * P * 16 + 3 * root * 16  # (up to four levels a pass)
     ms = res["mean_one_group"]["ms_per_call"]
     # parity at sampled times: the tree's mean against NumPy's, within the
     # rounding of a 15-level sum
