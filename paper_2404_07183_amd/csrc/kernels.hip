@@ -192,12 +192,12 @@ struct Chain {
     }
 };
 
-template <int K, typename T, int HK, typename Walk>
+template <int K, typename T, int HK, int E, typename Walk>
 __device__ __forceinline__ void chain_step(Chain<T, Walk> &ch, T &part, T p)
 {
     const T tP = ch.P.x, tQ = ch.tQ;
     const T y = min_raw(tP, tQ);
-    part = fma(hval<T, HK>(ch.P.y, ch.vQ, p), y - ch.x, part);
+    part = fma(hval<T, HK, E>(ch.P.y, ch.vQ, p), y - ch.x, part);
     ch.x = y;
     const bool c = tP <= tQ;
     ch.vQ = c ? ch.vQ : ch.P.y;
@@ -209,7 +209,7 @@ template <typename T, int HK, typename Walk, int... Ks>
 __device__ __forceinline__ void chain_block(Chain<T, Walk> &ch, T &part, T p,
                                             std::integer_sequence<int, Ks...>)
 {
-    (chain_step<Ks, T, HK>(ch, part, p), ...);
+    with_exponent<HK>(p, [&](auto e) { (chain_step<Ks, T, HK, e()>(ch, part, p), ...); });
     ch.w.end_block();
 }
 

@@ -236,12 +236,12 @@ template <typename T> struct StripChain {
     }
 };
 
-template <int K, typename T, int HK>
+template <int K, typename T, int HK, int E>
 __device__ __forceinline__ void strip_step(StripChain<T> &ch, T &part, T p)
 {
     const T tP = ch.P.x, tQ = ch.tQ;
     const T y = min_raw(tP, tQ);
-    part = fma(hval<T, HK>(ch.P.y, ch.vQ, p), y - ch.x, part);
+    part = fma(hval<T, HK, E>(ch.P.y, ch.vQ, p), y - ch.x, part);
     ch.x = y;
     const bool c = tP <= tQ;
     ch.vQ = c ? ch.vQ : ch.P.y;
@@ -253,7 +253,7 @@ template <typename T, int HK, int... Ks>
 __device__ __forceinline__ void strip_block(StripChain<T> &ch, T &part, T p,
                                             std::integer_sequence<int, Ks...>)
 {
-    (strip_step<Ks, T, HK>(ch, part, p), ...);
+    with_exponent<HK>(p, [&](auto e) { (strip_step<Ks, T, HK, e()>(ch, part, p), ...); });
     ch.w.end_block();
 }
 

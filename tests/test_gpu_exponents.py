@@ -1,0 +1,68 @@
+"""Integrals of |f - g|^p for whole and half p against the oracle, at the edges
+of the forms that the kernels compile them in: a fixed exponent up to 8 (5 for
+half p), then the exponent's bits for 9..15, 16..31, 32..63 and 64. Both pair
+kernels; equal values (h = 0), and differences whose power underflows.
+
+An FP64 or FP32 power by squaring and multiplying takes fewer than p roundings,
+the difference's own rounding counts p times, the width, the root and the
+sums' some more: (2 p + 40) ulps of the integral of |f - g|^p.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2404_07183_amd import api, workloads
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+WHOLE = [3, 4, 5, 6, 7, 8, 9, 15, 16, 31, 32, 63, 64]
+HALF = [1.5, 2.5, 3.5, 4.5, 5.5, 6.5, 7.5, 8.5, 15.5, 16.5, 31.5, 32.5, 63.5]
+
+
+def _set(n, dtype, scale):
+    o, t, v = workloads.uniform_counts(n, 20, 60, seed=n)
+    v = scale * np.round(8 * v) / 8  # differences of 0 among them
+    return workloads.to_dtype(o, t, v, dtype)
+
+
+def _is_strip(ws):
+    return int(ws.buf[192:196].cpu().numpy().view(np.int32)[0]) > 0
+
+
+@pytest.mark.parametrize("n", [40, 2003])
+@pytest.mark.parametrize("dtype,p", [(np.float64, p) for p in WHOLE + HALF] +
+                         [(np.float32, p) for p in WHOLE])
+def test_powers(dtype, p, n):
+    o, t, v = _set(n, dtype, 0.25)
+    X = api.PcfSet(o, t, v, device=DEV)
+    ws = api.Workspace()
+    M = api.pdist(X, float(p), power=True, workspace=ws).cpu().numpy().astype(np.float64)
+    assert _is_strip(ws) == (n == 2003)
+    rng = np.random.default_rng(int(2 * p))
+    I, J = rng.integers(0, n, 4000), rng.integers(0, n, 4000)
+    ref, ab = oracle.entries(oracle.LP_POW, float(p), o, t, v, I, J, with_abs=True)
+    err = np.abs(M[I, J] - ref)
+    assert np.all(err <= (2 * p + 40) * np.finfo(dtype).eps / 2 * np.maximum(ab, 1e-300))
+    assert np.all(np.diag(M) == 0) and np.array_equal(M, M.T)
+
+
+@pytest.mark.parametrize("p", [1.5, 2.5, 3.5, 5.5, 7.5, 63.5])
+def test_half_powers_at_the_ends_of_the_range(p):
+    # one piece each, width 1: h itself. Zero, subnormal and smallest normal
+    # differences, and some whose p-th power is near the smallest and the
+    # largest numbers
+    d = np.array([0.0, 5e-324, 1e-310, 2.0 ** -1022, 2.0 ** -1000, 2.0 ** -999,
+                  (2.0 ** -1000) ** (1 / p), (2.0 ** -900) ** (1 / p), 1e-3, 1.0, 3.0,
+                  (0.5 * np.finfo(np.float64).max) ** (1 / p)])
+    n = len(d) + 1
+    o = np.arange(n + 1) * 2
+    t = np.tile([0.0, 1.0], n)
+    v = np.zeros(2 * n)
+    v[2::2] = d
+    X = api.PcfSet(o, t, v, device=DEV)
+    got = api.pdist(X, p, power=True).cpu().numpy()[0, 1:]
+    with np.errstate(under="ignore"):
+        want = (d.astype(np.longdouble) ** np.longdouble(p)).astype(np.float64)
+    small = want < 1e-300
+    assert np.all(np.abs(got - want)[~small] <= ((2 * p + 40) * 2.0 ** -53 * want)[~small])
+    assert np.all((got >= 0) & (got < 2e-300) | ~small)
