@@ -99,9 +99,73 @@ __device__ __forceinline__ float pow_any(float x, float p)
 }
 __device__ __forceinline__ double pow_any(double x, double p) { return pow_series(x, p); }
 
+// One Horner step a z + c with c in scalar registers. (From fma the compiler
+// makes v_mov and v_fmac, two instructions, with all coefficients of both
+// series in vector registers.)
+__device__ __forceinline__ double horner(double a, double z, double c)
+{
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(z), "s"(c));
+    return r;
+}
+
+// pow_series for the steps of the forward kernels: the same series, without
+// branches (a branch in every step keeps the steps of a block apart), and with
+// the quotient s = (m - 1) / (m + 1), m + 1 in [1.7, 2.42), from the hardware's
+// reciprocal, one Newton step and the quotient's exact residual (within 0.501
+// ulp) in place of the general division. Strip kernel before / with it, 6,000
+// PCFs of 50 to 500 rows, FP64 p = 2.7: 33.8 / 26.0 ms (tile kernel before
+// 31.9).
+__device__ __forceinline__ double pow_steps(double x, double p)
+{
+    int e;
+    double m = frexp(x, &e);
+    const bool low = m < 0.70710678118654752440;
+    m = low ? m + m : m;
+    e = low ? e - 1 : e;
+    const double d = m + 1.0, n = m - 1.0;
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(fma(-d, r, 1.0), r, r);
+    double s = n * r;
+    s = fma(fma(-d, s, n), r, s);
+    const double z = s * s;
+    double q = horner(z, 1.0 / 23.0, 1.0 / 21.0);
+    q = horner(q, z, 1.0 / 19.0);
+    q = horner(q, z, 1.0 / 17.0);
+    q = horner(q, z, 1.0 / 15.0);
+    q = horner(q, z, 1.0 / 13.0);
+    q = horner(q, z, 1.0 / 11.0);
+    q = horner(q, z, 1.0 / 9.0);
+    q = horner(q, z, 1.0 / 7.0);
+    q = horner(q, z, 1.0 / 5.0);
+    q = horner(q, z, 1.0 / 3.0);
+    q = fma(q, z, 1.0);
+    const double y = p * fma(2.88539008177792681472 * s, q, (double)e);
+    const double k = rint(y);
+    const double g = (y - k) * 0.69314718055994530942;
+    double f = horner(g, 1.0 / 87178291200.0, 1.0 / 6227020800.0);
+    f = horner(f, g, 1.0 / 479001600.0);
+    f = horner(f, g, 1.0 / 39916800.0);
+    f = horner(f, g, 1.0 / 3628800.0);
+    f = horner(f, g, 1.0 / 362880.0);
+    f = horner(f, g, 1.0 / 40320.0);
+    f = horner(f, g, 1.0 / 5040.0);
+    f = horner(f, g, 1.0 / 720.0);
+    f = horner(f, g, 1.0 / 120.0);
+    f = horner(f, g, 1.0 / 24.0);
+    f = horner(f, g, 1.0 / 6.0);
+    f = fma(f, g, 0.5);
+    f = fma(f, g, 1.0);
+    f = fma(f, g, 1.0);
+    f = ldexp(f, (int)__builtin_fmax(__builtin_fmin(k, 1100.0), -1100.0));
+    f = y > 1025.0 ? (double)INFINITY : f;
+    return ((x == 0.0) | (y < -1080.0)) ? 0.0 : f;
+}
+__device__ __forceinline__ float pow_steps(float x, float p) { return pow_any(x, p); }
+
 // h(a, b); E: what is known at compile time of the integer exponent (kPowInt)
 // or of the integer below p (kPowHalf, at least 1), as in ipow_fixed; 0:
-// nothing.
+// nothing; kPow: 0 for pow_any, else pow_steps.
 template <typename T, int HK, int E = 0>
 __device__ __forceinline__ T hval(T a, T b, T p)
 {
@@ -120,6 +184,8 @@ __device__ __forceinline__ T hval(T a, T b, T p)
         return pow_half(fabs(a - b), p);
     } else if constexpr (HK == kPowInt) {
         return ipow(fabs(a - b), (int)p);
+    } else if constexpr (E != 0) {
+        return pow_steps(fabs(a - b), p);
     } else {
         return pow_any(fabs(a - b), p);
     }
@@ -158,6 +224,8 @@ __device__ __forceinline__ void with_exponent(T p, F f)
             return f(integral_constant<int, -6>());
         if (k == 64)
             return f(integral_constant<int, -7>());
+    } else if constexpr (HK == kPow) {
+        return f(integral_constant<int, 1>());
     }
     f(integral_constant<int, 0>());
 }

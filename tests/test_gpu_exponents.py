@@ -66,3 +66,22 @@ def test_half_powers_at_the_ends_of_the_range(p):
     small = want < 1e-300
     assert np.all(np.abs(got - want)[~small] <= ((2 * p + 40) * 2.0 ** -53 * want)[~small])
     assert np.all((got >= 0) & (got < 2e-300) | ~small)
+
+
+@pytest.mark.parametrize("p", [1.0625, 1.2, 2.7, 7.3, 40.1, 63.9])
+def test_series_powers(p):
+    # each power is within (|y| + 8) 2^-52 of itself, y = p log2 d; values in
+    # [0, 4) keep |y| below 12 p where the power counts
+    o, t, v = _set(2003, np.float64, 0.25)
+    X = api.PcfSet(o, t, v, device=DEV)
+    ws = api.Workspace()
+    M = api.pdist(X, p, power=True, workspace=ws).cpu().numpy()
+    assert _is_strip(ws)
+    small = api.pdist(api.PcfSet(o[:41], t[:o[40]], v[:o[40]], device=DEV), p, power=True)
+    rng = np.random.default_rng(9)
+    I, J = rng.integers(0, 2003, 4000), rng.integers(0, 2003, 4000)
+    ref, ab = oracle.entries(oracle.LP_POW, p, o, t, v, I, J, with_abs=True)
+    tol = (24 * p + 60) * 2.0 ** -53
+    assert np.all(np.abs(M[I, J] - ref) <= tol * np.maximum(ab, 1e-300))
+    assert np.all(np.abs(small.cpu().numpy() - M[:40, :40]) <= tol * M[:40, :40])
+    assert np.all(np.diag(M) == 0) and np.array_equal(M, M.T)
