@@ -360,14 +360,15 @@ __global__ __launch_bounds__(256) void red_split(RedFuseArgs a)
 // (with 512 threads the searches double and the pass takes 146 us; with 128,
 // 149 us: too few waves)
 constexpr int kFuseThreads = 256;
-constexpr int kFuseRun = kFuseTile / kFuseThreads;  // most rows a thread
+constexpr int kFuseRun = (kFuseTile + kFuseThreads - 1) / kFuseThreads;  // most rows a thread
+static_assert(kFuseRun * kFuseThreads >= kFuseTile, "a thread's run of a full tile");
 
 template <typename T> struct FuseNode {
     T before, after_v, after_t;  // value before the tile's rows; the row after them
 };
 
 template <typename T, int OP>
-__global__ __launch_bounds__(kFuseThreads) void red_fuse(RedFuseArgs a)
+__global__ __launch_bounds__(kFuseThreads, sizeof(T) == 8 ? 5 : 7) void red_fuse(RedFuseArgs a)
 {
     const T *__restrict__ tin = reinterpret_cast<const T *>(a.tin);
     const T *__restrict__ vin = reinterpret_cast<const T *>(a.vin);
