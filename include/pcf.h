@@ -49,7 +49,8 @@
  *    (from an earlier call on a set with identical offsets, window and kind)
  *    is reused and the call performs no host<->device copy and no
  *    synchronisation: it only launches kernels on `stream`, so it may be
- *    captured into a HIP graph.
+ *    captured into a HIP graph. A call that would make a plan is refused
+ *    while `stream` is capturing (PCF_EDEVICE, nothing launched).
  *  - No exception crosses the ABI. A non-OK status leaves a message for
  *    pcf_last_error() (thread-local).
  *  - Calls that overlap on one device and share a workspace race; give each
@@ -148,17 +149,17 @@ pcf_status pcf_gram(const pcf_set *X, void *out, int64_t ldo,
                     const pcf_window *w, void *ws, size_t ws_bytes,
                     uint32_t flags, void *stream);
 
-/* For callers that cannot allocate device memory (code under HIP graph
- * capture, tight serving loops, harnesses that forbid allocation):
- * pcf_pairwise_lp (kind PCF_LP or PCF_LP_POW) and pcf_gram (kind PCF_GRAM)
- * with the workspace taken from a device array the library holds, of
- * PCF_NOALLOC_SCRATCH_BYTES bytes on every GPU it runs on (held from module
- * load until the process ends), instead of a caller buffer. Same arguments,
- * results and errors as pcf_pairwise_lp, without ws and ws_bytes; calls no
- * allocating routine. PCF_ENOMEM (before any device work when
- * X->offsets_host is given) when the call's plan and packed records exceed
- * the array; PCF_EINVAL for PCF_REUSE_PLAN or PCF_RECORDS_PACKED, since every
- * call on a device shares that device's array and overwrites what it held.
+/* For callers that cannot allocate device memory (tight serving loops,
+ * harnesses that forbid allocation): pcf_pairwise_lp (kind PCF_LP or
+ * PCF_LP_POW) and pcf_gram (kind PCF_GRAM) with the workspace taken from a
+ * device array the library holds, of PCF_NOALLOC_SCRATCH_BYTES bytes on every
+ * GPU it runs on (held from module load until the process ends), instead of a
+ * caller buffer. Same arguments, results and errors as pcf_pairwise_lp,
+ * without ws and ws_bytes; calls no allocating routine. PCF_ENOMEM (before any
+ * device work when X->offsets_host is given) when the call's plan and packed
+ * records exceed the array; PCF_EINVAL for PCF_REUSE_PLAN or
+ * PCF_RECORDS_PACKED, since every call on a device shares that device's array
+ * and overwrites what it held; so no call of it can be captured.
  * Calls that overlap on one device (other streams or host threads) race;
  * calls in one stream are ordered. */
 #define PCF_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)

@@ -231,10 +231,19 @@ pcf_status upload_plan(const Plan &plan, int rec_bytes, void *ws,
     if (plan.rec_count >= ((int64_t)1 << 31))
         return fail(PCF_EUNSUPPORTED,
                     "more than 2^31 breakpoint records in one set");
+    // Refused under capture, for plans of every size: a captured plan is not in
+    // the workspace before the graph's first replay, where a call that reuses
+    // it would read it, and every replay would overwrite the plan of the calls
+    // since.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(s, &capture);
+    if (e == hipSuccess && capture != hipStreamCaptureStatusNone)
+        e = hipErrorStreamCaptureUnsupported;
+    if (e != hipSuccess)
+        return hip_fail(e, "a new plan (under capture: make it before, then PCF_REUSE_PLAN)");
     std::vector<unsigned char> buf;
     WsHeader hdr;
     plan_serialise(plan, rec_bytes, buf, hdr);
-    hipError_t e;
     if (buf.size() <= kArgPlanBytes) {
         e = launch_write_plan((unsigned char *)ws, buf.data(), (int64_t)buf.size(), s);
     } else {
