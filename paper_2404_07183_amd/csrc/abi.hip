@@ -146,6 +146,7 @@ struct PlanTag {
 struct PlanRecord {
     PlanTag tag;
     StripLaunch strips;  // waves > 0: a strip plan
+    PackShape pack;
 };
 std::mutex g_plan_mu;
 std::unordered_map<const void *, PlanRecord> g_plan_tags;
@@ -184,21 +185,31 @@ StripLaunch strip_launch(const Plan &plan, int rec_bytes)
     return l;
 }
 
-void remember_plan(const void *ws, const PlanTag &tag, const StripLaunch &strips)
+// The shape of the n PCFs of host offsets `ho`.
+PackShape pack_shape(const int64_t *ho, int64_t n)
 {
-    std::lock_guard<std::mutex> lock(g_plan_mu);
-    g_plan_tags[ws] = {tag, strips};
+    PackShape p;
+    p.rows = ho[n] - ho[0];
+    for (int64_t i = 0; i < n; ++i)
+        p.longest = std::max(p.longest, ho[i + 1] - ho[i]);
+    return p;
 }
 
-pcf_status check_reused_plan(const void *ws, const PlanTag &tag, StripLaunch &strips)
+void remember_plan(const void *ws, const PlanRecord &r)
+{
+    std::lock_guard<std::mutex> lock(g_plan_mu);
+    g_plan_tags[ws] = r;
+}
+
+pcf_status check_reused_plan(const void *ws, const PlanTag &tag, PlanRecord &r)
 {
     std::lock_guard<std::mutex> lock(g_plan_mu);
     auto it = g_plan_tags.find(ws);
     if (it == g_plan_tags.end())
         return fail(PCF_EINVAL, "PCF_REUSE_PLAN: this workspace holds no plan made by "
                                 "this library");
-    const PlanTag &h = it->second.tag;
-    strips = it->second.strips;
+    r = it->second;
+    const PlanTag &h = r.tag;
     if (h.kind != tag.kind) {
         static const char *names[] = {"a matrix call", "pcf_pairwise_backward",
                                       "pcf_pairwise_batched", "pcf_cross"};
@@ -221,7 +232,7 @@ constexpr size_t kArgPlanBytes = 3 * sizeof(PlanChunk);
 
 // Copy a plan's header, blocks and segments into the workspace.
 pcf_status upload_plan(const Plan &plan, int rec_bytes, void *ws,
-                       size_t ws_bytes, hipStream_t s, const PlanTag &tag)
+                       size_t ws_bytes, hipStream_t s, const PlanRecord &r)
 {
     const int64_t need = plan_workspace_bytes(plan, rec_bytes);
     if ((int64_t)ws_bytes < need)
@@ -253,7 +264,7 @@ pcf_status upload_plan(const Plan &plan, int rec_bytes, void *ws,
     }
     if (e != hipSuccess)
         return hip_fail(e, "uploading the tile plan");
-    remember_plan(ws, tag, strip_launch(plan, rec_bytes));
+    remember_plan(ws, r);
     return PCF_OK;
 }
 
@@ -295,23 +306,23 @@ pcf_status prepare(const pcf_set *X, const Plan *plan, void *ws,
     c.reuse = (flags & PCF_REUSE_PLAN) != 0;
     c.validate = (flags & PCF_VALIDATE) != 0;
     c.P = ho ? ho[X->n] : -1;
+    PlanRecord r;
+    pcf_status st;
     if (!c.reuse) {
-        pcf_status st = upload_plan(*plan, rec_bytes_of(X->dtype), ws,
-                                    ws_bytes, s, tag);
-        if (st != PCF_OK)
-            return st;
-        c.strips = strip_launch(*plan, rec_bytes_of(X->dtype));
+        r = {tag, strip_launch(*plan, rec_bytes_of(X->dtype)), pack_shape(ho, X->n)};
+        st = upload_plan(*plan, rec_bytes_of(X->dtype), ws, ws_bytes, s, r);
     } else {
-        pcf_status st = check_reused_plan(ws, tag, c.strips);
-        if (st != PCF_OK)
-            return st;
+        st = check_reused_plan(ws, tag, r);
     }
+    if (st != PCF_OK)
+        return st;
+    c.strips = r.strips;
     if (c.validate) {
         if (c.P < 0)
             return fail(PCF_EINVAL, "PCF_VALIDATE needs host offsets when "
                                     "the plan is reused");
         int64_t bad = -1;
-        pcf_status st = run_validation(X, (unsigned char *)ws, c.P, s, &bad);
+        st = run_validation(X, (unsigned char *)ws, c.P, s, &bad);
         if (st != PCF_OK)
             return st;
         if (bad >= 0)
@@ -327,10 +338,9 @@ pcf_status prepare(const pcf_set *X, const Plan *plan, void *ws,
     if (flags & PCF_RECORDS_PACKED) {
         e = launch_reset(w, s);
     } else {
-        const int64_t mean = c.P >= 0 ? c.P / X->n : 0;
         e = X->dtype == PCF_F64
-                ? launch_pack<double>(X->offsets, X->n, X->t, X->v, w, mean, s)
-                : launch_pack<float>(X->offsets, X->n, X->t, X->v, w, mean, s);
+                ? launch_pack<double>(X->offsets, X->n, X->t, X->v, w, r.pack, s)
+                : launch_pack<float>(X->offsets, X->n, X->t, X->v, w, r.pack, s);
     }
     if (e != hipSuccess)
         return hip_fail(e, "packing breakpoint records");
@@ -1214,7 +1224,9 @@ pcf_status pcf_cross(const pcf_set *X, const pcf_set *Y, pcf_kind kind, double p
     if ((int64_t)ws_bytes < need)
         return fail(PCF_ENOMEM, "workspace too small: need " + std::to_string(need) +
                                     " bytes, got " + std::to_string(ws_bytes));
-    st = upload_plan(plan, rb, ws, ws_bytes, s, plan_tag(kPlanCross, X, nullptr, ldo, flags));
+    const StripLaunch strips = strip_launch(plan, rb);
+    st = upload_plan(plan, rb, ws, ws_bytes, s,
+                     {plan_tag(kPlanCross, X, nullptr, ldo, flags), strips, PackShape()});
     if (st != PCF_OK)
         return st;
     unsigned char *w = (unsigned char *)ws;
@@ -1237,18 +1249,18 @@ pcf_status pcf_cross(const pcf_set *X, const pcf_set *Y, pcf_kind kind, double p
     // one record array: X's records, then Y's (starting past X's records and
     // padding), indexed through the combined offsets
     int64_t *coff = reinterpret_cast<int64_t *>(w + at);
-    const int64_t px = comb[X->n], py = comb[X->n + Y->n] - px;
-    const int64_t ybase = px + X->n * kPad;
+    const PackShape px = pack_shape(comb.data(), X->n);
+    const PackShape py = pack_shape(comb.data() + X->n, Y->n);
+    const int64_t ybase = px.rows + X->n * kPad;
     hipError_t e = launch_concat_offsets(X->offsets, X->n, Y->offsets, Y->n, coff, s);
-    const int64_t mx = px / X->n, my = py / Y->n;
     if (e == hipSuccess)
         e = X->dtype == PCF_F64
-                ? launch_pack<double>(X->offsets, X->n, X->t, X->v, w, mx, s, 0)
-                : launch_pack<float>(X->offsets, X->n, X->t, X->v, w, mx, s, 0);
+                ? launch_pack<double>(X->offsets, X->n, X->t, X->v, w, px, s, 0)
+                : launch_pack<float>(X->offsets, X->n, X->t, X->v, w, px, s, 0);
     if (e == hipSuccess)
         e = X->dtype == PCF_F64
-                ? launch_pack<double>(Y->offsets, Y->n, Y->t, Y->v, w, my, s, ybase)
-                : launch_pack<float>(Y->offsets, Y->n, Y->t, Y->v, w, my, s, ybase);
+                ? launch_pack<double>(Y->offsets, Y->n, Y->t, Y->v, w, py, s, ybase)
+                : launch_pack<float>(Y->offsets, Y->n, Y->t, Y->v, w, py, s, ybase);
     if (e != hipSuccess)
         return hip_fail(e, "packing breakpoint records");
 
@@ -1267,7 +1279,6 @@ pcf_status pcf_cross(const pcf_set *X, const pcf_set *Y, pcf_kind kind, double p
         hk = lp_hkind(p, X->dtype == PCF_F64);
         a.root = (kind == PCF_LP_POW || p == 1.0) ? 0 : (p == 2.0 ? 1 : 2);
     }
-    const StripLaunch strips = strip_launch(plan, rb);
     e = strips.waves > 0
             ? launch_strips(X->dtype == PCF_F64, hk, a, strips, s)
             : launch_forward(X->dtype == PCF_F64, hk, a, tile_grid(&plan, false), s);

@@ -75,10 +75,10 @@ __global__ void write_plan(PlanChunk c, unsigned char *ws, int32_t at, int32_t w
 // ---------------------------------------------------------------------------
 // Pack CSR (t, v) rows into breakpoint records (see the file comment), L
 // lanes a PCF, so that a row's PCF is known without a search of the offsets
-// (6.97 million rows of 35,000 PCFs, FP64: 147 us with the search per row,
-// 54 us now). The set's records start at record rec_base (0, or past a
-// first set's records when two sets share one record array). Also resets the
-// tile counters for the kernel that follows.
+// (7 million rows of 35,000 PCFs, FP64: 93 us with a search per row, 36 us so).
+// The set's records start at record rec_base (0, or past a first set's records
+// when two sets share one record array). Also resets the tile counters for the
+// kernel that follows.
 template <typename T, int L>
 __global__ __launch_bounds__(256) void pack_records(const int64_t *__restrict__ offsets,
                                                     int64_t n, const T *__restrict__ t,
@@ -102,6 +102,56 @@ __global__ __launch_bounds__(256) void pack_records(const int64_t *__restrict__ 
             x.t = k + 1 < m ? t[o + k + 1] : S;
             x.v = v[o + (k < m ? k : m - 1)];
             r[k] = x;
+        }
+    }
+}
+
+// The same with a wave for every kPackRows consecutive rows, whatever PCFs they
+// belong to (found by one search a wave): sets with PCFs too long for a wave
+// each.
+constexpr int64_t kPackRows = 512;
+template <typename T>
+__global__ __launch_bounds__(256) void pack_rows(const int64_t *__restrict__ offsets, int64_t n,
+                                                 const T *__restrict__ t,
+                                                 const T *__restrict__ v, unsigned char *ws,
+                                                 int64_t rec_base)
+{
+    WsHeader &h = *reinterpret_cast<WsHeader *>(ws);
+    if (blockIdx.x == 0 && threadIdx.x < kXcds)
+        h.counter[threadIdx.x] = 0u;
+    Rec<T> *rec = reinterpret_cast<Rec<T> *>(ws + h.off_rec) + rec_base;
+    const T S = sentinel<T>();
+    const int lane = threadIdx.x & 63;
+    const int64_t P = offsets[n], waves = (int64_t)gridDim.x * 4;
+    for (int64_t r0 = (blockIdx.x * (int64_t)4 + (threadIdx.x >> 6)) * kPackRows; r0 < P;
+         r0 += waves * kPackRows) {
+        const int64_t r1 = r0 + kPackRows < P ? r0 + kPackRows : P;
+        // the PCF of row r0, 64 candidates a round
+        int64_t i = 0, width = n;
+        while (width > 1) {
+            const int64_t step = (width + 63) / 64;
+            const bool le = lane * step < width && offsets[i + lane * step] <= r0;
+            const int got = __popcll(__ballot(le));  // at least 1
+            const int64_t skip = (got > 0 ? got - 1 : 0) * step;
+            i += skip;
+            width = width - skip < step ? width - skip : step;
+        }
+        int64_t o = offsets[i], e = offsets[i + 1];
+        for (;;) {
+            const int64_t next = i + 2 <= n ? offsets[i + 2] : P;
+            // (the padding goes with the PCF's last row)
+            const int64_t stop = e <= r1 ? e + kPad : r1;
+            for (int64_t k = (o > r0 ? o : r0) + lane; k < stop; k += 64) {
+                Rec<T> x;
+                x.t = k + 1 < e ? t[k + 1] : S;
+                x.v = v[k < e ? k : e - 1];
+                rec[k + i * kPad] = x;
+            }
+            if (e >= r1 || i + 1 >= n)
+                break;
+            ++i;
+            o = e;
+            e = next;
         }
     }
 }
@@ -473,24 +523,40 @@ size_t tile_shared_bytes(int rec_bytes, bool backward)
     return (size_t)kSharedHead + (size_t)(kLdsRecordBytes / rec_bytes) * rec_bytes;
 }
 
-// mean: rows a PCF on average, where known (0: not)
+// A wave takes 0.14 us and more for 64 rows of its PCF, one after the other, so
+// from kPackLong rows on the launch waits for its longest PCF. PCFs / rows form,
+// FP64, us: 1,000 PCFs of 50 rows and one of 1,000 4.1 / 7.3, of 2,000 6.4 / 7.5,
+// of 16,000 38 / 7.4; 40,000 of 25 and two of 1,000 12.6 / 18, of 2,000 16 / 18,
+// of 8,000 42 / 19; 35,000 of 200 and one of 1,000 36 / 39, of 2,000 39 / 39, of
+// 50,000 265 / 39; 64 of 4,000 13.7 / 4.5; two of 500,000 2,396 / 5.9.
+constexpr int64_t kPackLong = 2000;
+// Sixteen lanes a PCF where most of a wave's would have no row and no PCF needs
+// many rounds of them: 40,000 PCFs of 25 rows, 64 / 16 lanes, 9.8 / 7.3 us, with
+// two of 500 among them 10.1 / 14.4.
+constexpr int64_t kPackFew = 256;
+
 template <typename T>
-hipError_t launch_pack(const int64_t *offsets, int64_t n, const void *t,
-                       const void *v, unsigned char *ws, int64_t mean,
-                       hipStream_t s, int64_t rec_base)
+hipError_t launch_pack(const int64_t *offsets, int64_t n, const void *t, const void *v,
+                       unsigned char *ws, const PackShape &shape, hipStream_t s,
+                       int64_t rec_base)
 {
-    // (16 lanes a PCF where most of a wave's would have no row)
-    const bool few = mean > 0 && mean + kPad <= 32;
+    const bool few = shape.rows + n * kPad <= 32 * n && shape.longest <= kPackFew;
+    const bool rows = shape.longest >= kPackLong;
+    const int64_t units = rows ? (shape.rows + kPackRows - 1) / kPackRows : n;
     const int64_t per = few ? 16 : 4;
-    int64_t blocks = (n + per - 1) / per;
+    int64_t blocks = (units + per - 1) / per;
     if (blocks > 16384)
         blocks = 16384;
-    if (few)
-        hipLaunchKernelGGL((pack_records<T, 16>), dim3((unsigned)blocks), dim3(256), 0, s,
-                           offsets, n, (const T *)t, (const T *)v, ws, rec_base);
+    const dim3 g((unsigned)blocks), blk(256);
+    const T *tt = (const T *)t, *vv = (const T *)v;
+    if (rows)
+        hipLaunchKernelGGL(pack_rows<T>, g, blk, 0, s, offsets, n, tt, vv, ws, rec_base);
+    else if (few)
+        hipLaunchKernelGGL((pack_records<T, 16>), g, blk, 0, s, offsets, n, tt, vv, ws,
+                           rec_base);
     else
-        hipLaunchKernelGGL((pack_records<T, 64>), dim3((unsigned)blocks), dim3(256), 0, s,
-                           offsets, n, (const T *)t, (const T *)v, ws, rec_base);
+        hipLaunchKernelGGL((pack_records<T, 64>), g, blk, 0, s, offsets, n, tt, vv, ws,
+                           rec_base);
     return hipGetLastError();
 }
 
@@ -617,10 +683,10 @@ hipError_t launch_forward(bool f64, int hk, const FwdArgs &a, int grid,
 }
 
 template hipError_t launch_pack<float>(const int64_t *, int64_t, const void *,
-                                       const void *, unsigned char *, int64_t,
+                                       const void *, unsigned char *, const PackShape &,
                                        hipStream_t, int64_t);
 template hipError_t launch_pack<double>(const int64_t *, int64_t, const void *,
-                                        const void *, unsigned char *, int64_t,
+                                        const void *, unsigned char *, const PackShape &,
                                         hipStream_t, int64_t);
 template hipError_t launch_validate<float>(const int64_t *, int64_t,
                                            const void *, const void *,

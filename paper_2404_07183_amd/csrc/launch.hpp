@@ -48,12 +48,15 @@ struct BwdArgs {
                              // launch_adj_finish (needs launch_adj_bounds first)
 };
 
-// Packs a set's records and resets the tile counters (mean: rows a PCF on
-// average, 0 when not known).
+// A set's rows and the rows of its longest PCF, which choose how it is packed.
+struct PackShape {
+    int64_t rows = 0, longest = 0;
+};
+// Packs a set's records (n > 0) and resets the tile counters.
 template <typename T>
-hipError_t launch_pack(const int64_t *offsets, int64_t n, const void *t,
-                       const void *v, unsigned char *ws, int64_t mean,
-                       hipStream_t s, int64_t rec_base = 0);
+hipError_t launch_pack(const int64_t *offsets, int64_t n, const void *t, const void *v,
+                       unsigned char *ws, const PackShape &shape, hipStream_t s,
+                       int64_t rec_base = 0);
 // A plan's bytes (a multiple of 4) as kernel arguments, a few KiB a launch.
 struct PlanChunk {
     uint32_t word[896];
