@@ -541,7 +541,7 @@ struct RedPlan {
     int64_t n = 0, P = 0, C = 0;  // PCFs, rows, chunks
     // groups (B+1), chunk rows (C), chunk groups (C), the fused passes' bundles
     std::vector<int64_t> meta;
-    std::vector<RedPass> passes;  // none: L single levels (0 or 1)
+    std::vector<RedPass> passes;  // none: L single levels
     size_t off_split = 0;
     size_t off_ccnt = 0, off_coff = 0, off_buf[4] = {0, 0, 0, 0}, off_q = 0, off_map = 0;
     size_t off_kb = 0;  // PCF_REDUCE_STD: each chunk's first rows (64 per chunk)
@@ -597,8 +597,17 @@ pcf_status red_plan(const pcf_set *X, int32_t B, const int64_t *groups, int op,
     for (int32_t b = 0; b < B; ++b)
         rp.C += (ho[groups[b + 1]] - ho[groups[b]] + kRedChunkRows - 1) / kRedChunkRows;
     int64_t entries = (int64_t)B + 1 + 2 * rp.C;
-    // more than one level: passes of up to kFuseLevels levels, evenly
-    const int npass = rp.L > 1 ? (rp.L + kFuseLevels - 1) / kFuseLevels : 0;
+    // more than one level: passes of up to kFuseLevels levels, evenly, where
+    // the bundles are few or have the rows for it
+    int npass = rp.L > 1 ? (rp.L + kFuseLevels - 1) / kFuseLevels : 0;
+    if (npass > 0) {
+        const int depth = (rp.L + npass - 1) / npass;
+        int64_t nbundles = 0;
+        for (int32_t b = 0; b < B; ++b)
+            nbundles += (groups[b + 1] - groups[b] + ((int64_t)1 << depth) - 1) >> depth;
+        if (nbundles > kFuseFew && rp.P < kFuseRows * nbundles)
+            npass = 0;
+    }
     int64_t most_tiles = 0;  // (a bound from the rows and items)
     for (int q = 0, level = 0; q < npass; ++q) {
         RedPass ps;
@@ -1477,7 +1486,7 @@ void red_roots(const pcf_set *X, const RedPlan &rp, unsigned char *w, const void
         rt = X->t;
         rv = X->v;
     } else {
-        const int k = rp.passes.empty() ? 0 : (int)(rp.passes.size() - 1) % 2;
+        const int k = (int)(rp.passes.empty() ? rp.L - 1 : rp.passes.size() - 1) % 2;
         rt = w + rp.off_buf[2 * k];
         rv = w + rp.off_buf[2 * k + 1];
     }
@@ -1527,23 +1536,24 @@ static pcf_status reduce_rows_impl(const pcf_set *X, int32_t B,
         a.split = (int64_t *)(w + rp.off_split);
         e = launch_red_fuse(f64, (int)op, a, s);
     }
-    if (e == hipSuccess && rp.L == 1) {
-        // one level (and the combinations of two sets): no pass to share
+    if (e == hipSuccess && rp.passes.empty() && rp.L > 0) {
         int32_t *row_pcf = (int32_t *)(w + rp.off_map);
         e = launch_red_rowmap(X->offsets, rp.n, row_pcf, s);
-        RedLevelArgs a;
-        a.offsets = X->offsets;
-        a.groups = meta;
-        a.row_pcf = row_pcf;
-        a.n = rp.n;
-        a.B = B;
-        a.level = 0;
-        a.tin = X->t;
-        a.vin = X->v;
-        a.tout = w + rp.off_buf[0];
-        a.vout = w + rp.off_buf[1];
-        if (e == hipSuccess)
+        for (int l = 0; l < rp.L && e == hipSuccess; ++l) {
+            RedLevelArgs a;
+            a.offsets = X->offsets;
+            a.groups = meta;
+            a.row_pcf = row_pcf;
+            a.n = rp.n;
+            a.B = B;
+            a.level = l;
+            const int ki = (l + 1) % 2, ko = l % 2;  // level l writes buffer pair l % 2
+            a.tin = l == 0 ? X->t : (const void *)(w + rp.off_buf[2 * ki]);
+            a.vin = l == 0 ? X->v : (const void *)(w + rp.off_buf[2 * ki + 1]);
+            a.tout = w + rp.off_buf[2 * ko];
+            a.vout = w + rp.off_buf[2 * ko + 1];
             e = launch_red_level(f64, (int)op, a, rp.P, s);
+        }
     }
     const void *rt, *rv;
     red_roots(X, rp, w, rt, rv);

@@ -30,6 +30,15 @@ constexpr int kFuseSpacing = 48;  // rows between a list's samples
 constexpr int kFuseRanks = 24;    // samples between tile starts
 constexpr int kFuseTile = kFuseRanks * kFuseSpacing + kFuseLists * kFuseSpacing;
 constexpr int kFuseSplit = kFuseLists + 1;
+// The fused passes are taken for at most kFuseFew bundles in the first one or
+// from kFuseRows rows a bundle on average: a bundle takes a workgroup of its own
+// at least, and its entry of the host's table. Means, FP64, whole calls, single
+// levels / fused, us: 33,333 groups of 3 PCFs, 60 rows a bundle 491 / 865; 8,032
+// of 3, 249 rows 212 / 265; 5,000 of 16, 400 rows 326 / 314; 1,893 of 33 (3
+// bundles each), 512 rows 345 / 356; 2,861 of 3, 699 rows 168 / 168; 1,818 of 4,
+// 1,100 rows 178 / 159; 100 of 16, 192 rows 133 / 81; 3,000 of 16, 192 rows 229 /
+// 207; 1,000 of 60 (4,000 bundles), 192 rows 245 / 278.
+constexpr int64_t kFuseRows = 512, kFuseFew = 3000;
 struct RedBundle {
     int64_t p0, pend;       // its PCFs (one output item)
     int64_t sample0, tile0; // its first sample and tile
