@@ -1233,6 +1233,9 @@ pcf_status pcf_cross(const pcf_set *X, const pcf_set *Y, pcf_kind kind, double p
     if ((int64_t)ws_bytes < need)
         return fail(PCF_ENOMEM, "workspace too small: need " + std::to_string(need) +
                                     " bytes, got " + std::to_string(ws_bytes));
+    // (before the upload, which waits for the stream)
+    const PackShape px = pack_shape(comb.data(), X->n);
+    const PackShape py = pack_shape(comb.data() + X->n, Y->n);
     const StripLaunch strips = strip_launch(plan, rb);
     st = upload_plan(plan, rb, ws, ws_bytes, s,
                      {plan_tag(kPlanCross, X, nullptr, ldo, flags), strips, PackShape()});
@@ -1258,8 +1261,6 @@ pcf_status pcf_cross(const pcf_set *X, const pcf_set *Y, pcf_kind kind, double p
     // one record array: X's records, then Y's (starting past X's records and
     // padding), indexed through the combined offsets
     int64_t *coff = reinterpret_cast<int64_t *>(w + at);
-    const PackShape px = pack_shape(comb.data(), X->n);
-    const PackShape py = pack_shape(comb.data() + X->n, Y->n);
     const int64_t ybase = px.rows + X->n * kPad;
     hipError_t e = launch_concat_offsets(X->offsets, X->n, Y->offsets, Y->n, coff, s);
     if (e == hipSuccess)
