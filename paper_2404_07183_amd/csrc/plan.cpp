@@ -127,25 +127,68 @@ constexpr double strip_ring(int rec_bytes, int64_t mean)
 //   FP32 rows 800: K 1000 153 / 188  K 3000  430 / 414   K 40000  5031 / 4527
 // Tiles of short PCFs are bounded by their PCF count and fill LDS badly;
 // elsewhere a strip's jobs must outweigh their starts and ends.
-// `spread` is the mean square of the row counts over their squared mean:
-// columns of very different lengths make waves wait for the oldest one's place
-// in the ring (128 problems of geometric row counts, spread 2: 2350 / 2500).
+// `spread` is the mean square of the row counts over their squared mean, and
+// so spread times mean the length of the PCF that a step belongs to: columns
+// of very different lengths make waves wait for the oldest one's place in the
+// ring. That decides where the columns of all waves are long against LDS (7,000
+// PCFs: 1 % of 2,500 rows among 20, FP64 2896 / 4270; 0.5 % of 2,000 among 40, FP64
+// 2013 / 2079, FP32 1972 / 2229; 3 % of 600 among 30, FP64 2469 / 2063) or the gain
+// is small (10 % of 400 among 100, 2,500 PCFs 485 / 535; 1 % of 3,000 among 700, 600
+// PCFs 325 / 368; 128 problems of geometric row counts, spread 2, 2350 / 2500).
 // A strip plan also takes the host longer to make and to copy, by about 25 us
 // and 5 us more for every thousand PCFs. With short PCFs, whose gain goes with
 // the pairs a lane, that decides for sets used once (L1 FP64, rows 46, tile
 // kernel / strip kernel, us, set used again and new): 1,600 PCFs 126 / 125 and
 // 133 / 157; 2,200 229 / 182 and 237 / 221; 3,000 381 / 294 and 390 / 331; a
 // window of 600 rows and 4,400 columns 195 / 188 and 209 / 244.
-bool strips_pay(double mean, double spread, double K, double lane_pairs, int64_t pcfs,
-                int rec_bytes)
+bool strips_pay(double mean, double spread, double longest, double K, double lane_pairs,
+                int64_t pcfs, int rec_bytes)
 {
-    if (mean <= 64.0)
-        return K >= 200.0 && lane_pairs >= 3.0 + (double)pcfs / 600.0;
-    if (spread > 1.6)
+    const double n = (double)pcfs;
+    const bool f64 = rec_bytes == 16;
+    if (mean < 100.0 && spread * mean > (f64 ? 400.0 : 550.0))
         return false;
-    if (rec_bytes == 16)
-        return K >= (mean >= 600.0 ? 300.0 : (mean >= 300.0 ? 800.0 : 3000.0));
-    return K >= (mean >= 600.0 ? 3000.0 : 16000.0);
+    if (mean <= 64.0)
+        return K >= 200.0 && lane_pairs >= 3.0 + n / 600.0;
+    if (spread > (f64 && mean >= 100.0 && mean < 300.0 ? 1.3 : 1.6) ||
+        (mean >= 100.0 && longest > 4.0 * mean))
+        return false;
+    if (!f64)
+        return K >= (mean >= 600.0 ? 3000.0 : 16000.0);
+    return K >= (mean >= 600.0 ? 300.0 : (mean >= 300.0 ? 800.0 : 3000.0));
+}
+
+// The most rows of a block, so that no column takes the wave that merges it
+// with the block longer than a share of the whole launch: the steps of a lane
+// against those the launch has for each (a pair counts 64 steps more, what else
+// it costs). 64 rows where that is within 0.3 of them, else rows for 0.2. (The
+// first rows of a triangle are no columns of another block.) Tile kernel, 64
+// rows, rows so bounded, us: 2,000 PCFs, 1 % of 600 rows among 30, FP64 203 / 242 /
+// 169, FP32 171 / 192 / 125; 5 % of 400 among 20 228 / 321 / 195 and 185 / 238 / 126;
+// 3,000 PCFs, 3 % of 800 among 20, FP32 441 / 495 / 377; 2,003 of geometric counts
+// and four of 900, FP64 185 / 201 / 142. Tiles are faster below 12 rows (3,000 PCFs,
+// four of 3,000 rows among 40, FP32, 11 rows 324 / 400 / 386) and where one column
+// fills a sixth of LDS, so that fewer rows leave no room for more columns at a
+// time (the same, FP64, 27 rows 406 / 410 / 446).
+constexpr int64_t kStripTailRows = 12;
+int64_t strip_tail_rows(const int64_t *offsets, const std::vector<Region> &regions, double mean,
+                        double lane_pairs, int64_t longest_bytes)
+{
+    if (mean >= 100.0)  // (no column much longer than the others: strips_pay)
+        return kStripMaxRows;
+    int64_t column = 1;
+    for (const Region &g : regions) {
+        const bool tri = g.map.type == kSegTriangle;
+        const bool tall = g.rb - g.ra > g.cb - g.ca;  // (its rows stream)
+        const int64_t a = tri ? g.ra + kStripMaxRows : (tall ? g.ra : g.ca);
+        const int64_t b = tri || tall ? g.rb : g.cb;
+        for (int64_t i = a; i < b; ++i)
+            column = std::max(column, offsets[i + 1] - offsets[i]);
+    }
+    const double rows = lane_pairs * (2.0 * mean + 64.0) * 64.0 / (double)column;
+    if (0.3 * rows >= (double)kStripMaxRows)
+        return kStripMaxRows;
+    return 6 * longest_bytes > kStripLdsBytes ? 0 : (int64_t)(0.2 * rows);
 }
 
 // Strip plan of the regions over PCFs [lo, hi); false where the tile plan is
@@ -174,8 +217,12 @@ bool build_strips(const int64_t *offsets, int64_t lo, int64_t hi,
     const double mean_steps = 2.0 * (double)(mean - kPad);
     const double rows = (double)(offsets[hi] - offsets[lo]) / (double)(hi - lo);
     const double lane_pairs = pairs / (64.0 * cus * kStripWaves);
-    if (!strips_pay(rows, squares / (double)(hi - lo) / (rows * rows), lane_pairs * mean_steps,
-                    lane_pairs, hi - lo, rec_bytes))
+    if (!strips_pay(rows, squares / (double)(hi - lo) / (rows * rows), (double)(longest - kPad),
+                    lane_pairs * mean_steps, lane_pairs, hi - lo, rec_bytes))
+        return false;
+    const int64_t tail_rows =
+        strip_tail_rows(offsets, regions, rows, lane_pairs, longest * rec_bytes);
+    if (tail_rows < kStripTailRows)
         return false;
     int waves = kStripWaves;
     int64_t R = 0, M = 1, ring = 0, area = 0;
@@ -184,8 +231,9 @@ bool build_strips(const int64_t *offsets, int64_t lo, int64_t hi,
         const double run = std::min({K, std::sqrt(2.0 * K * kItemSteps), 400.0});
         const double item = std::max(1.0, run * 64.0 / mean_steps);  // pairs
         int64_t most = shape.max_block >= kMaxBlock ? kStripMaxRows : shape.max_block;
-        most = std::max<int64_t>(1, std::min(most, (int64_t)item));
-        for (M = 1;; ++M) {
+        most = std::max<int64_t>(1, std::min({most, (int64_t)item, tail_rows}));
+        auto fit = [&](int64_t cols) {
+            M = cols;
             R = most;
             for (int it = 0; it < 3; ++it) {  // (the rows a block gets depend on the
                                               // waves' areas, and they on the rows)
@@ -199,12 +247,19 @@ bool build_strips(const int64_t *offsets, int64_t lo, int64_t hi,
                 // mean)
                 R = std::max<int64_t>(1, std::min(most, area * 13 / 10 / mean));
             }
-            // (another column only where a full row block is too little work)
-            if (R < kStripMaxRows || (double)(R * (M + 1)) > item + 1.0 ||
-                R * (M + 1) > kStripMaxPairs || M + 1 > kStripMaxCols)
+            return area >= longest && area >= 4 * mean;
+        };
+        bool fits = fit(1);
+        // (another column only where a full row block is too little work, and
+        // the longest PCF still fits beside it)
+        while (fits && R >= std::min<int64_t>(kStripMaxRows, tail_rows) && (double)(R * (M + 1)) <= item + 1.0 &&
+               R * (M + 1) <= kStripMaxPairs && M < kStripMaxCols) {
+            if (!fit(M + 1)) {
+                fit(M - 1);
                 break;
+            }
         }
-        if (area >= longest && area >= 4 * mean)
+        if (fits)
             break;
     }
     if (waves < 4)
@@ -226,9 +281,12 @@ bool build_strips(const int64_t *offsets, int64_t lo, int64_t hi,
     plan.groups.reserve(most_groups);
     gcost.reserve(most_groups);
     plan.sblocks.reserve((size_t)nblk);
+    std::vector<int32_t> longs;  // groups far longer than the others
     uint32_t virt = 0;
     int64_t at = 0;  // virt modulo the ring
     auto place = [&](int64_t start, int64_t cols, int64_t len) {
+        if (len > 3 * M * mean)
+            longs.push_back((int32_t)plan.groups.size());
         if (at + len > ring) {  // no group crosses the ring's end
             virt += (uint32_t)(ring - at);
             at = 0;
@@ -371,11 +429,18 @@ bool build_strips(const int64_t *offsets, int64_t lo, int64_t hi,
                     plan.groups[(size_t)gend].virt - plan.groups[(size_t)g0].virt < (1u << 28))
                     lo_ = gend;
                 plan.jobs.push_back({(int32_t)q, b, (int32_t)g0, (int32_t)lo_});
-                used += kJobSteps * waves + range_cost(rows, rowrows, g0, lo_);
+                // (a job lasts at least as long as its longest item, which one
+                // wave merges while the others wait)
+                const double work = range_cost(rows, rowrows, g0, lo_);
+                double cost = work;
+                for (auto l = std::lower_bound(longs.begin(), longs.end(), (int32_t)g0);
+                     l != longs.end() && *l < lo_; ++l)
+                    cost = std::max(cost, waves * range_cost(rows, rowrows, *l, *l + 1));
+                used += kJobSteps * waves + cost;
+                left -= kJobSteps * waves + work;
                 g0 = lo_;
                 if (used >= 0.9 * target) {
                     plan.runs.push_back((int32_t)plan.jobs.size());
-                    left -= used;
                     used = 0.0;
                     next_target();
                 }
