@@ -28,22 +28,26 @@ void build_blocks(const int64_t *offsets, int64_t lo, int64_t hi,
 {
     std::sort(cuts.begin(), cuts.end());
     size_t ci = 0;
-    int64_t count = 0, recs = 0;
-    for (int64_t i = lo; i < hi; ++i) {
-        const int64_t r = offsets[i + 1] - offsets[i] + kPad;
-        bool is_cut = false;
-        while (ci < cuts.size() && cuts[ci] <= i) {
-            if (cuts[ci] == i)
-                is_cut = true;
+    for (int64_t i = lo; i < hi;) {
+        blocks.push_back((int32_t)i);
+        while (ci < cuts.size() && cuts[ci] <= i)
             ++ci;
+        int64_t most = std::min(hi, i + std::max(max_block, 1));
+        if (ci < cuts.size())
+            most = std::min(most, cuts[ci]);
+        // the most PCFs within the budget (at least one)
+        const int64_t limit = offsets[i] + i * kPad + budget;
+        int64_t e = i + 1;
+        if (offsets[most] + most * kPad <= limit)
+            e = most;
+        while (e < most) {
+            const int64_t mid = (e + most + 1) / 2;
+            if (offsets[mid] + mid * kPad <= limit)
+                e = mid;
+            else
+                most = mid - 1;
         }
-        if (count == 0 || is_cut || count == max_block || recs + r > budget) {
-            blocks.push_back((int32_t)i);
-            count = 0;
-            recs = 0;
-        }
-        ++count;
-        recs += r;
+        i = e;
     }
 }
 
@@ -136,11 +140,13 @@ constexpr double strip_ring(int rec_bytes, int64_t mean)
 // is small (10 % of 400 among 100, 2,500 PCFs 485 / 535; 1 % of 3,000 among 700, 600
 // PCFs 325 / 368; 128 problems of geometric row counts, spread 2, 2350 / 2500).
 // A strip plan also takes the host longer to make and to copy, by about 25 us
-// and 5 us more for every thousand PCFs. With short PCFs, whose gain goes with
-// the pairs a lane, that decides for sets used once (L1 FP64, rows 46, tile
-// kernel / strip kernel, us, set used again and new): 1,600 PCFs 126 / 125 and
-// 133 / 157; 2,200 229 / 182 and 237 / 221; 3,000 381 / 294 and 390 / 331; a
-// window of 600 rows and 4,400 columns 195 / 188 and 209 / 244.
+// and 5 us more for every thousand PCFs. Where that outweighs the gain of a
+// short launch it decides for sets used once (L1 FP64, us, calls in a stream
+// and alone): rows 46, 1,600 PCFs 126 / 125 and 133 / 157; 2,200 229 / 182 and
+// 237 / 221; 600 x 4,400 195 / 188 and 209 / 244. Rows 100, 600 x 6,600 470 / 478
+// and 507 / 541; 2,850 PCFs 501 / 470 and 522 / 515. Rows 200, 100 x 20,000 520 /
+// 500 and 599 / 630; rows 275, 301 x 5,003 527 / 488 and 605 / 604; rows 400, 50 x
+// 5,500 234 / 248 and 276 / 313; 820 PCFs 270 / 250 and 295 / 286.
 bool strips_pay(double mean, double spread, double longest, double K, double lane_pairs,
                 int64_t pcfs, int rec_bytes)
 {
@@ -155,7 +161,9 @@ bool strips_pay(double mean, double spread, double longest, double K, double lan
         return false;
     if (!f64)
         return K >= (mean >= 600.0 ? 3000.0 : 16000.0);
-    return K >= (mean >= 600.0 ? 300.0 : (mean >= 300.0 ? 800.0 : 3000.0));
+    if (mean >= 300.0)
+        return K >= (mean >= 600.0 ? 300.0 : 800.0) + n / 25.0;
+    return K >= (mean >= 150.0 ? 2700.0 : 2850.0) + n / 12.5;
 }
 
 // The most rows of a block, so that no column takes the wave that merges it
@@ -275,11 +283,9 @@ bool build_strips(const int64_t *offsets, int64_t lo, int64_t hi,
     // column groups: at most M PCFs, within one block, at their ring places
     const int64_t most_recs = std::max(longest, M * mean * 5 / 4);
     std::vector<int32_t> gfirst((size_t)nblk + 1);
-    std::vector<double> gcost;  // rows of the groups before each
     const size_t most_groups = (size_t)(M == 1 ? hi - lo : (hi - lo) * 2 / M + nblk) + 1;
     plan.groups.clear();
     plan.groups.reserve(most_groups);
-    gcost.reserve(most_groups);
     plan.sblocks.reserve((size_t)nblk);
     std::vector<int32_t> longs;  // groups far longer than the others
     uint32_t virt = 0;
@@ -293,7 +299,6 @@ bool build_strips(const int64_t *offsets, int64_t lo, int64_t hi,
         }
         plan.groups.push_back({(int32_t)start, (int32_t)(offsets[start] + start * kPad),
                                (int32_t)(len + (cols << kStripColShift)), virt});
-        gcost.push_back((double)(offsets[start] - offsets[lo]));
         virt += (uint32_t)len;
         at += len;
     };
@@ -316,7 +321,6 @@ bool build_strips(const int64_t *offsets, int64_t lo, int64_t hi,
     }
     gfirst[(size_t)nblk] = (int32_t)plan.groups.size();
     plan.groups.push_back({(int32_t)hi, 0, 0, virt});
-    gcost.push_back((double)(offsets[hi] - offsets[lo]));
 
     plan.strips = true;
     plan.strip_waves = waves;
@@ -328,12 +332,11 @@ bool build_strips(const int64_t *offsets, int64_t lo, int64_t hi,
     // order, cut into runs (a workgroup's work between two tickets). One run a
     // CU unless the launch is long (then the queue evens out what the cost
     // misses); a run that crosses row blocks holds several jobs.
-    // (a block's cost over groups [g0, g1) by prefix sums of group records)
+    // (a block's cost over groups [g0, g1) by the offsets of their first PCFs)
     auto range_cost = [&](int64_t rows, int64_t rowrows, int64_t g0, int64_t g1) {
-        const double m = (double)(plan.groups[(size_t)g1].start - plan.groups[(size_t)g0].start);
+        const int64_t c0 = plan.groups[(size_t)g0].start, c1 = plan.groups[(size_t)g1].start;
         return (double)(g1 - g0) * kItemSteps +
-               ((double)rows * (gcost[(size_t)g1] - gcost[(size_t)g0]) + m * (double)rowrows) /
-                   64.0;
+               (double)(rows * (offsets[c1] - offsets[c0]) + (c1 - c0) * rowrows) / 64.0;
     };
     double total = 0.0, items = 0.0;
     for (Region &g : regions) {

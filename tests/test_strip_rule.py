@@ -1,0 +1,92 @@
+"""Where the planner (csrc/plan.cpp) takes the strip kernel, on the CPU: a short
+launch over many PCFs, whose plan costs the host more than the kernel gains, keeps
+its tile plan, and the same steps over fewer PCFs do not; and the row blocks by
+bisection are those of a scan."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2404_07183_amd", "csrc")
+
+HARNESS = r"""
+#include "plan.hpp"
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+#include <random>
+using namespace pcf;
+#define CHECK(c) do { if (!(c)) { std::printf("line %d: %s\n", __LINE__, #c); std::exit(1); } } while (0)
+
+static std::mt19937 g(3);
+static int64_t U(int64_t a, int64_t b) { return a + (int64_t)(g() % (uint64_t)(b - a + 1)); }
+
+// whether nx PCFs against ny (0: nx PCFs among themselves) of about `rows` rows
+// are planned as strips
+static bool strips(int64_t nx, int64_t ny, int64_t rows, int rec_bytes)
+{
+    const int64_t n = nx + ny;
+    std::vector<int64_t> o(1, 0);
+    for (int64_t i = 0; i < n; ++i)
+        o.push_back(o.back() + U(rows / 2, rows + rows / 2));
+    Plan p;
+    std::string e;
+    CHECK(plan_matrix(n, o.data(), rec_bytes, false, ny > 0, 0, nx, nx, n, false,
+                      ny > 0 ? ny : n, TileShape(), p, e, 256));
+    return p.strips;
+}
+
+static void scan_blocks(const int64_t *offsets, int64_t lo, int64_t hi,
+                        std::vector<int64_t> cuts, int64_t budget, int32_t max_block,
+                        std::vector<int32_t> &blocks)
+{
+    int64_t count = 0, recs = 0;
+    for (int64_t i = lo; i < hi; ++i) {
+        const int64_t r = offsets[i + 1] - offsets[i] + kPad;
+        if (count == 0 || std::count(cuts.begin(), cuts.end(), i) || count == max_block ||
+            recs + r > budget) {
+            blocks.push_back((int32_t)i);
+            count = recs = 0;
+        }
+        ++count;
+        recs += r;
+    }
+}
+
+int main()
+{
+    CHECK(!strips(100, 20000, 200, 16) && strips(600, 12000, 200, 16));
+    CHECK(!strips(300, 6600, 200, 16) && strips(2500, 0, 200, 16));
+    CHECK(!strips(600, 6600, 100, 16) && !strips(2000, 2010, 100, 16) && strips(3500, 0, 100, 16));
+    CHECK(!strips(50, 5500, 400, 16) && !strips(512, 520, 400, 16));
+    CHECK(strips(200, 2700, 400, 16) && strips(820, 0, 410, 16));
+    CHECK(!strips(246, 247, 650, 16) && strips(450, 0, 650, 16));
+    for (int it = 0; it < 2000; ++it) {
+        const int64_t n = U(1, 300), lo = U(0, n - 1), hi = U(lo, n);
+        std::vector<int64_t> o(1, 0), cuts;
+        for (int64_t i = 0; i < n; ++i)
+            o.push_back(o.back() + (U(0, 20) == 0 ? U(1, 900) : U(1, 40)));
+        for (int k = (int)U(0, 6); k > 0; --k)
+            cuts.push_back(U(0, n));
+        std::vector<int32_t> a, b;
+        const int64_t budget = U(1, 1200);
+        const int32_t most = (int32_t)U(1, 64);
+        build_blocks(o.data(), lo, hi, cuts, budget, most, a);
+        scan_blocks(o.data(), lo, hi, cuts, budget, most, b);
+        CHECK(a == b);
+    }
+    std::printf("ok\n");
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_rule(tmp_path):
+    src, exe = tmp_path / "rule_check.cpp", tmp_path / "rule_check"
+    src.write_text(HARNESS)
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-I", CSRC, "-o", str(exe), str(src),
+                           os.path.join(CSRC, "plan.cpp")])
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout
