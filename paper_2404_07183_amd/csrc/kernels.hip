@@ -41,6 +41,7 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <set>
 #include <utility>
@@ -106,15 +107,14 @@ __global__ __launch_bounds__(256) void pack_records(const int64_t *__restrict__ 
     }
 }
 
-// The same with a wave for every kPackRows consecutive rows, whatever PCFs they
+// The same with a wave for every `per` consecutive rows, whatever PCFs they
 // belong to (found by one search a wave): sets with PCFs too long for a wave
 // each.
-constexpr int64_t kPackRows = 512;
 template <typename T>
 __global__ __launch_bounds__(256) void pack_rows(const int64_t *__restrict__ offsets, int64_t n,
                                                  const T *__restrict__ t,
                                                  const T *__restrict__ v, unsigned char *ws,
-                                                 int64_t rec_base)
+                                                 int64_t rec_base, int64_t per)
 {
     WsHeader &h = *reinterpret_cast<WsHeader *>(ws);
     if (blockIdx.x == 0 && threadIdx.x < kXcds)
@@ -123,9 +123,9 @@ __global__ __launch_bounds__(256) void pack_rows(const int64_t *__restrict__ off
     const T S = sentinel<T>();
     const int lane = threadIdx.x & 63;
     const int64_t P = offsets[n], waves = (int64_t)gridDim.x * 4;
-    for (int64_t r0 = (blockIdx.x * (int64_t)4 + (threadIdx.x >> 6)) * kPackRows; r0 < P;
-         r0 += waves * kPackRows) {
-        const int64_t r1 = r0 + kPackRows < P ? r0 + kPackRows : P;
+    for (int64_t r0 = (blockIdx.x * (int64_t)4 + (threadIdx.x >> 6)) * per; r0 < P;
+         r0 += waves * per) {
+        const int64_t r1 = r0 + per < P ? r0 + per : P;
         // the PCF of row r0, 64 candidates a round
         int64_t i = 0, width = n;
         while (width > 1) {
@@ -525,11 +525,14 @@ size_t tile_shared_bytes(int rec_bytes, bool backward)
 
 // A wave takes 0.14 us and more for 64 rows of its PCF, one after the other, so
 // from kPackLong rows on the launch waits for its longest PCF. PCFs / rows form,
-// FP64, us: 1,000 PCFs of 50 rows and one of 1,000 4.1 / 7.3, of 2,000 6.4 / 7.5,
-// of 16,000 38 / 7.4; 40,000 of 25 and two of 1,000 12.6 / 18, of 2,000 16 / 18,
-// of 8,000 42 / 19; 35,000 of 200 and one of 1,000 36 / 39, of 2,000 39 / 39, of
-// 50,000 265 / 39; 64 of 4,000 13.7 / 4.5; two of 500,000 2,396 / 5.9.
+// FP64, us: 1,000 PCFs of 50 rows and one of 1,000 4.1 / 3.8, of 2,000 6.4 / 3.8,
+// of 16,000 38 / 3.9; 40,000 of 25 and two of 1,000 12.6 / 13, of 2,000 16.8 / 13,
+// of 16,000 78 / 13; 35,000 of 200 and one of 1,000 36 / 39, of 2,000 38 / 39, of
+// 16,000 98 / 39; 64 of 8,000 25.8 / 4.7; two of 500,000 2,341 / 6. A wave's run of
+// rows: 64 where they are few (7,004 PCFs, 226,000 rows, runs of 64 / 128 / 512 5.5 /
+// 6.2 / 11.4), up to 512 (7 million rows, FP64 47 / 38 / 39, FP32 41 / 30 / 23).
 constexpr int64_t kPackLong = 2000;
+constexpr int64_t kPackRows = 512, kPackWaves = 8192;
 // Sixteen lanes a PCF where most of a wave's would have no row and no PCF needs
 // many rounds of them: 40,000 PCFs of 25 rows, 64 / 16 lanes, 9.8 / 7.3 us, with
 // two of 500 among them 10.1 / 14.4.
@@ -542,7 +545,9 @@ hipError_t launch_pack(const int64_t *offsets, int64_t n, const void *t, const v
 {
     const bool few = shape.rows + n * kPad <= 32 * n && shape.longest <= kPackFew;
     const bool rows = shape.longest >= kPackLong;
-    const int64_t units = rows ? (shape.rows + kPackRows - 1) / kPackRows : n;
+    const int64_t run =
+        std::min(kPackRows, std::max<int64_t>(64, (shape.rows / kPackWaves + 63) / 64 * 64));
+    const int64_t units = rows ? (shape.rows + run - 1) / run : n;
     const int64_t per = few ? 16 : 4;
     int64_t blocks = (units + per - 1) / per;
     if (blocks > 16384)
@@ -550,7 +555,7 @@ hipError_t launch_pack(const int64_t *offsets, int64_t n, const void *t, const v
     const dim3 g((unsigned)blocks), blk(256);
     const T *tt = (const T *)t, *vv = (const T *)v;
     if (rows)
-        hipLaunchKernelGGL(pack_rows<T>, g, blk, 0, s, offsets, n, tt, vv, ws, rec_base);
+        hipLaunchKernelGGL(pack_rows<T>, g, blk, 0, s, offsets, n, tt, vv, ws, rec_base, run);
     else if (few)
         hipLaunchKernelGGL((pack_records<T, 16>), g, blk, 0, s, offsets, n, tt, vv, ws,
                            rec_base);

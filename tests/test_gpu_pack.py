@@ -29,6 +29,7 @@ COUNTS = {
     "search of two rounds": [2] * 64 + [3000] + [1] * 4000,
     "search of three rounds": [3] * 4096 + [2500] + [7] * 3000 + [1],
     "very long": [1, 100003, 2, 60000, 30],
+    "longer runs": [700001, 64, 128, 1, 420000, 127, 65],
 }
 
 
