@@ -127,7 +127,10 @@ constexpr double strip_ring(int rec_bytes, int64_t mean)
 //   FP64 rows 200: K 1000 180 / 195  K 3000  480 / 474   K 40000  5929 / 5125
 //   FP64 rows 400: K 1000 253 / 232  K 3000  731 / 579   K 40000  9093 / 6400
 //   FP32 rows  50: K 300  78 /  73   K 3000  656 / 374   K 40000  8331 / 3661
-//   FP32 rows 200: K 1000 134 / 145  K 3000  322 / 335   K 40000  3510 / 3090
+//   FP32 rows  85: K 1500 207 / 195  K 3000  402 / 330   K 12000  1483 / 1066
+//   FP32 rows 120: K 1500 181 / 187  K 3000  333 / 313   K 12000  1307 / 1022
+//   FP32 rows 150: K 1500 169 / 188  K 3000  315 / 327   K  6000   612 /  553
+//   FP32 rows 200: K 1500 161 / 189  K 6000  552 / 555   K 12000  1076 / 1000
 //   FP32 rows 800: K 1000 153 / 188  K 3000  430 / 414   K 40000  5031 / 4527
 // Tiles of short PCFs are bounded by their PCF count and fill LDS badly;
 // elsewhere a strip's jobs must outweigh their starts and ends.
@@ -146,7 +149,9 @@ constexpr double strip_ring(int rec_bytes, int64_t mean)
 // 237 / 221; 600 x 4,400 195 / 188 and 209 / 244. Rows 100, 600 x 6,600 470 / 478
 // and 507 / 541; 2,850 PCFs 501 / 470 and 522 / 515. Rows 200, 100 x 20,000 520 /
 // 500 and 599 / 630; rows 275, 301 x 5,003 527 / 488 and 605 / 604; rows 400, 50 x
-// 5,500 234 / 248 and 276 / 313; 820 PCFs 270 / 250 and 295 / 286.
+// 5,500 234 / 248 and 276 / 313; 820 PCFs 270 / 250 and 295 / 286. FP32, rows 100,
+// 300 x 13,107 362 / 349 and 422 / 463; 2,804 PCFs 360 / 332 and 392 / 376; rows 150,
+// 300 x 17,476 611 / 588 and 680 / 712.
 bool strips_pay(double mean, double spread, double longest, double K, double lane_pairs,
                 int64_t pcfs, int rec_bytes)
 {
@@ -156,11 +161,14 @@ bool strips_pay(double mean, double spread, double longest, double K, double lan
         return false;
     if (mean <= 64.0)
         return K >= 200.0 && lane_pairs >= 3.0 + n / 600.0;
-    if (spread > (f64 && mean >= 100.0 && mean < 300.0 ? 1.3 : 1.6) ||
+    if (spread > (mean < 100.0 || mean >= 300.0 ? 1.6 : (f64 ? 1.3 : 1.4)) ||
         (mean >= 100.0 && longest > 4.0 * mean))
         return false;
-    if (!f64)
-        return K >= (mean >= 600.0 ? 3000.0 : 16000.0);
+    if (!f64) {
+        if (mean >= 200.0)
+            return K >= (mean >= 600.0 ? 3000.0 : 16000.0);
+        return K >= (mean >= 150.0 ? 5700.0 : (mean >= 100.0 ? 2700.0 : 2500.0)) + n / 12.5;
+    }
     if (mean >= 300.0)
         return K >= (mean >= 600.0 ? 300.0 : 800.0) + n / 25.0;
     return K >= (mean >= 150.0 ? 2700.0 : 2850.0) + n / 12.5;

@@ -63,6 +63,10 @@ int main()
     CHECK(!strips(50, 5500, 400, 16) && !strips(512, 520, 400, 16));
     CHECK(strips(200, 2700, 400, 16) && strips(820, 0, 410, 16));
     CHECK(!strips(246, 247, 650, 16) && strips(450, 0, 650, 16));
+    CHECK(strips(3041, 0, 85, 8) && !strips(2150, 0, 85, 8) && !strips(300, 18724, 70, 8));
+    CHECK(strips(2804, 0, 100, 8) && !strips(300, 13107, 100, 8) && strips(2804, 2804, 100, 8));
+    CHECK(strips(3300, 0, 155, 8) && !strips(2289, 0, 155, 8) && !strips(300, 17476, 155, 8));
+    CHECK(!strips(3965, 0, 205, 8) && strips(5000, 0, 205, 8));
     for (int it = 0; it < 2000; ++it) {
         const int64_t n = U(1, 300), lo = U(0, n - 1), hi = U(lo, n);
         std::vector<int64_t> o(1, 0), cuts;
