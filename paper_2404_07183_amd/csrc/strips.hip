@@ -616,8 +616,10 @@ __global__ __launch_bounds__(kThreads) void pairwise_strips(FwdArgs args)
         // load for the next job while the other waves finish (once it is
         // known: its fields are written before valid)
         const int32_t known = *(lds_i32)(size_t)lds_address(&sh.job[cur ^ 1].valid);
-        if (known > 0)
+        if (known > 0) {
+            asm volatile("" ::: "memory");  // (the fields after valid)
             load_job(sh.job[cur ^ 1]);
+        }
         sync_lds();
         if (known < 0 && sh.job[cur ^ 1].valid)
             load_job(sh.job[cur ^ 1]);
