@@ -9,7 +9,8 @@
 // 2j and 2j+1 (each covering 2^l consecutive PCFs) are merged into item j of
 // level l+1, and an unpaired last item moves up unchanged. Every group takes
 // the same ceil(log2 M_max) levels, up to four of them in one pass for all
-// groups (red_fuse); a tree of one level takes red_level.
+// groups (red_fuse), or, where the groups are many and short (kFuseFew,
+// kFuseRows) and for trees of one level, a launch a level (red_level).
 //
 // Merge without compaction. A level keeps every position of the merged
 // breakpoint lists (ties: the first list first), so item j of level l+1

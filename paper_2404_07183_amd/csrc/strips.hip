@@ -16,10 +16,10 @@
 // is short, dependent and full of latency, 41 % of an FP64 tile. Here a
 // SIMD's waves drift apart and one wave's latency is covered by the others'
 // merges. What bounds it (20,000 PCFs of 50 to 500 rows, L1 FP64, counters):
-// LDS 89 % of the time, 60 % of that in bank conflicts of the records' random
+// LDS 87 % of the time, 59 % of that in bank conflicts of the records' random
 // 16-byte reads (16 lanes on 16 slots collide three deep on average), VALU
-// 79 %; the tile kernel: 75 % and 71 %. Kernel times, tile kernel / this one:
-// that matrix 63.8 / 57.3 ms; FP64 PCFs of 400 rows on average, 5,120 of them,
+// 78 % (tile kernel 70 %). Kernel times, tile kernel / this one: that matrix
+// 63.4 / 57.3 ms; FP64 PCFs of 400 rows on average, 5,120 of them,
 // 9.09 / 6.40 ms; of 25 rows, 20,480, 12.4 / 6.4 ms (a tile's 32 x 32 PCFs
 // leave most of LDS empty there); FP32, 100 to 1000 rows, a window of 1,500 x
 // 12,000, 5.33 / 4.78 ms. Sixteen waves a workgroup against twelve: 5 to 20 %
