@@ -273,7 +273,7 @@ bool build_strips(const int64_t *offsets, int64_t lo, int64_t hi,
         bool fits = fit(1);
         // (another column only where a full row block is too little work, and
         // the longest PCF still fits beside it)
-        while (fits && R >= std::min<int64_t>(kStripMaxRows, tail_rows) && (double)(R * (M + 1)) <= item + 1.0 &&
+        while (fits && R >= tail_rows && (double)(R * (M + 1)) <= item + 1.0 &&
                R * (M + 1) <= kStripMaxPairs && M < kStripMaxCols) {
             if (!fit(M + 1)) {
                 fit(M - 1);
